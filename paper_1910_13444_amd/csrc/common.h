@@ -165,7 +165,7 @@ enum EpiMode { EPI_FWD = 0, EPI_BWD = 1, EPI_DF = 2 };
 template <class T> struct NtArgs {
   const T* X;  int64_t x_g;  int64_t ldx;  // A operand rows (activations)
   const T* Wm; int64_t w_g;  int64_t ldw;  // B operand rows: [N x K] row-major
-  const float* bias; int64_t b_g;         // EPI_FWD: bias on stream 0 (may be null)
+  const float* bias; int64_t b_g;         // EPI_FWD: bias on stream 0
   T* out_a;  T* out_h; int64_t o_g; int64_t ldo;  // EPI_FWD: pre-activation / activation
   const T* aprev;                          // EPI_BWD: saved pre-activation of the layer below
   T* out_da;                               // EPI_BWD: its pre-activation cotangent

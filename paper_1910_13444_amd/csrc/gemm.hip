@@ -40,6 +40,9 @@ namespace pigan {
 // LDS bank-conflict counter; a padded pitch without the swizzle conflicted on
 // the writes).
 static constexpr int LDS_PITCH = 64;
+// registers of accumulators, fragments and saved pre-activations up to which the
+// ring kernels read their fragments one chunk ahead
+static constexpr int PIPE_REGS = 200;
 typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -79,6 +82,101 @@ __device__ __forceinline__ void load4(const T* p, float* v) {
   } else {
     const float4 a = *(const float4*)p;
     v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+  }
+}
+
+// A 32 x 32 product fragment against rows in memory.  The matrix core leaves
+// lane l with point l & 31 and four consecutive columns per register group q
+// (8 q + 4 (l >> 5) ..).  Two lane exchanges turn that into 16-byte row pieces
+// of which four lanes (l, l + 32, l + 16, l + 48) cover 64 consecutive bytes:
+// v_permlane32_swap_b32 (16-bit storage only: gathers eight columns per lane),
+// then v_permlane16_swap_b32, which trades the second piece of point p with
+// the first piece of point p + 16.  Piece pair i, half j of a lane is then
+// point (l & 15) + 16 j, columns FragPos::col(i) ...  Both swaps are their own
+// inverse, so loads run the same steps backwards.  (32-byte pieces, without
+// the second exchange, made the forward stores of five streams slower than
+// staging whole rows through LDS: 1.82 against 1.76 ms at K = N = 512,
+// 256,064 points; 64-byte pieces take neither barrier nor LDS.)
+template <class T> struct FragRaw { u32x4 w[sizeof(T) == 2 ? 1 : 2][2]; };
+
+__device__ __forceinline__ void swap32(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+__device__ __forceinline__ void swap16(u32x4& a, u32x4& b) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const auto r = __builtin_amdgcn_permlane16_swap(a[e], b[e], false, false);
+    a[e] = r[0];
+    b[e] = r[1];
+  }
+}
+
+// first column of the lane's piece in pair i (of a fragment's 32 columns)
+template <class T>
+__device__ __forceinline__ int frag_col(int lane, int i) {
+  return sizeof(T) == 2 ? 16 * ((lane >> 4) & 1) + 8 * (lane >> 5) : 16 * i + 8 * ((lane >> 4) & 1) + 4 * (lane >> 5);
+}
+
+template <class T>
+__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
+  return (uint32_t)__builtin_bit_cast(uint16_t, Elem<T>::from_f(lo)) |
+         ((uint32_t)__builtin_bit_cast(uint16_t, Elem<T>::from_f(hi)) << 16);
+}
+
+// products layout -> pieces
+template <class T>
+__device__ __forceinline__ void frag_pack(FragRaw<T>& f, const f32x16& v) {
+  if constexpr (sizeof(T) == 2) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int b = 8 * j;
+      uint32_t a0 = pack2<T>(v[b], v[b + 1]), a1 = pack2<T>(v[b + 2], v[b + 3]);
+      uint32_t b0 = pack2<T>(v[b + 4], v[b + 5]), b1 = pack2<T>(v[b + 6], v[b + 7]);
+      swap32(a0, b0);
+      swap32(a1, b1);
+      f.w[0][j] = u32x4{a0, a1, b0, b1};
+    }
+    swap16(f.w[0][0], f.w[0][1]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f.w[i][j][e] = __float_as_uint(v[8 * i + 4 * j + e]);
+      swap16(f.w[i][0], f.w[i][1]);
+    }
+  }
+}
+
+// pieces -> products layout: first the lane exchanges of the whole fragment,
+// then the lane's values of register group q
+template <class T>
+__device__ __forceinline__ void frag_unswap(FragRaw<T>& f) {
+#pragma unroll
+  for (int i = 0; i < (sizeof(T) == 2 ? 1 : 2); ++i) swap16(f.w[i][0], f.w[i][1]);
+  if constexpr (sizeof(T) == 2) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        uint32_t x = f.w[0][j][c], y = f.w[0][j][2 + c];
+        swap32(x, y);
+        f.w[0][j][c] = x;
+        f.w[0][j][2 + c] = y;
+      }
+  }
+}
+template <class T>
+__device__ __forceinline__ void frag_group(const FragRaw<T>& f, int q, float* v) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if constexpr (sizeof(T) == 2)
+      v[e] = Elem<T>::to_f(__builtin_bit_cast(T, (uint16_t)(f.w[0][q >> 1][2 * (q & 1) + (e >> 1)] >> (16 * (e & 1)))));
+    else
+      v[e] = __uint_as_float(f.w[q >> 1][q & 1][e]);
   }
 }
 
@@ -141,16 +239,20 @@ __device__ __forceinline__ void wait_vmcnt() {
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
-// NS > 0 (16-bit types): the operand stages move from global memory straight
-// into an NS-deep LDS ring (global_load_lds_dwordx4, no register staging),
-// issued NS - 1 stages ahead of the multiply, so that the load latency is
-// covered by several stages of matrix-core work.
+// RING (16-bit types): the operand stages move from global memory straight
+// into two LDS buffers (global_load_lds_dwordx4, no register staging), one
+// stage ahead of the multiply.  A stage is 128 bytes of every row, loaded as
+// two 64-byte slices back to back: a cache line then crosses from L2 once
+// (measured with every block reading L2-resident rows: 18.3 TB/s over the chip
+// for single 64-byte slices, 34.8 TB/s in pairs).
+// TWO (with RING): two-term weights.  A k slice of X is staged once and used
+// by two stages of weights, the low terms and the high terms.
 // PM (fp32 storage only): products from bf16 pieces of the fp32 operands
 // (ProdMode); PM_SPLIT3 folds the accumulators into fp64 after every stage.
-// p.kx > 0 (two-term weights): operand X is kx wide and is read twice, the
-// weight rows are 2 kx wide.
+// p.kx > 0 (two-term weights): operand X is kx wide, the weight rows are
+// 2 kx wide (without TWO, X is read twice).
 template <class T, int ND1, int ND2, int WM, int WN, int MT, int NT, int EPI, int OCC, bool DB = (OCC >= 2),
-          int NS = 0, int PM = PM_NATIVE, int NB = 2>
+          bool RING = false, int PM = PM_NATIVE, int NB = 2, bool TWO = false>
 __global__ void __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(OCC)))
 k_gemm_nt(const NtArgs<T> p) {
   constexpr int C = 1 + ND1 + ND2;
@@ -161,15 +263,15 @@ k_gemm_nt(const NtArgs<T> p) {
   constexpr int KS = 64 / ES;                      // k values per stage
   constexpr int NCH = 64 / (16 * ES);              // 16-wide chunks per stage
   constexpr int ROWS = C * BM + BN;
-  constexpr int STAGE = ROWS * LDS_PITCH;          // bytes of one operand stage
+  constexpr int STAGE = ROWS * LDS_PITCH;          // bytes of one operand stage (RING: of one of its two slices)
   constexpr int PIECES = ROWS * 4;
   constexpr int PPT = (PIECES + NTH - 1) / NTH;
-  constexpr int OPITCH = BN * ES + 16;             // epilogue staging pitch (bytes)
-  constexpr int OUTB = BM * OPITCH;
-  constexpr int RING = (NS > 0 ? NS : 2) * STAGE;
-  constexpr int LDSB = RING > OUTB ? RING : OUTB;
-  static_assert(NS == 0 || (ES == 2 && NS >= 2 && ROWS % 16 == 0), "direct-to-LDS stages: 16-bit types");
+  constexpr int XBUF = 2 * C * BM * LDS_PITCH, WBUF = 2 * BN * LDS_PITCH;   // RING buffers
+  constexpr int OUTB = PM == PM_F64 ? BM * 65 * 4 : 0;   // fp64 products are re-laid out through LDS
+  constexpr int LDSB = RING ? 2 * (XBUF + WBUF) : (2 * STAGE > OUTB ? 2 * STAGE : OUTB);
+  static_assert(!RING || (ES == 2 && PM == PM_NATIVE), "direct-to-LDS stages: 16-bit types");
   static_assert(PM == PM_NATIVE || ES == 4, "split products: fp32 storage");
+  static_assert(!TWO || (RING && EPI == EPI_FWD), "two-term stages: ring kernels, forward products");
   // fp32 mode (fp32 storage, products not split into bf16): tanh in fp64
   constexpr bool X64 = ES == 4 && PM != PM_SPLIT2 && PM != PM_SPLIT3;
   typedef typename Elem<T>::frag frag;
@@ -205,7 +307,7 @@ k_gemm_nt(const NtArgs<T> p) {
   const char* src[PPT];
   bool valid[PPT], isx[PPT];
 #pragma unroll
-  for (int i = 0; i < (NS > 0 ? 0 : PPT); ++i) {
+  for (int i = 0; i < (RING ? 0 : PPT); ++i) {
     const int piece = tid + i * NTH;
     const int row = piece >> 2, sg = piece & 3;
     valid[i] = UNCOND;
@@ -225,6 +327,43 @@ k_gemm_nt(const NtArgs<T> p) {
         src[i] = Wb + (int64_t)n * p.ldw * (int64_t)ES + sg * 16;
       }
     }
+  }
+
+  // the lane's part of the outputs: hh selects the column half of every
+  // fragment, mloc the point within the block (the epilogue's layout)
+  const int hh = lane >> 5;
+  auto mloc = [&](int u) { return 32 * (MT * wm + u) + (lane & 31); };
+  auto ncol = [&](int t, int q) { return 32 * (wn * NT + t) + 8 * q + 4 * hh; };   // column within the block
+  auto fcol = [&](int t) { return n0 + 32 * (wn * NT + t); };                      // first column of a fragment
+  // point of the lane's half j of fragment u (frag_pack's layout)
+  auto fpt = [&](int u, int j) { return m0 + 32 * (MT * wm + u) + (lane & 15) + 16 * j; };
+  // the pieces of fragment (u, t) of stream k of an array laid out as the
+  // outputs; points past the segment end and columns past N take valid elements
+  auto load_frag = [&](FragRaw<T>& f, const T* base, int u, int k, int t) {
+    const int nb = fcol(t) < p.N ? fcol(t) : 0;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      int64_t pt = fpt(u, j);
+      if (pt > npts - 1) pt = npts - 1;
+      const T* row = base + g * p.o_g + (p.seg.row0 + k * p.seg.plane + pt) * p.ldo + nb;
+#pragma unroll
+      for (int i = 0; i < (ES == 2 ? 1 : 2); ++i) f.w[i][j] = *(const u32x4*)(row + frag_col<T>(lane, i));
+    }
+  };
+
+  // reverse pass: the saved pre-activations the epilogue needs.  PRE: where
+  // the registers allow it they are read before the products, so that their
+  // latency is covered by them
+  constexpr bool PRE = EPI == EPI_BWD && RING && MT * C * NT * 24 <= 160;
+  FragRaw<T> apre[PRE ? MT : 1][PRE ? C : 1][PRE ? NT : 1];
+  if constexpr (PRE) {
+#pragma unroll
+    for (int u = 0; u < MT; ++u)
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int k = 0; k < C; ++k) load_frag(apre[u][k][t], p.aprev, u, k, t);
+    __builtin_amdgcn_sched_barrier(0);
   }
 
   f32x16 acc[MT][C][NT];
@@ -423,75 +562,130 @@ k_gemm_nt(const NtArgs<T> p) {
     }
   };
 
-  if constexpr (NS > 0) {
+  if constexpr (RING) {
     // One DMA instruction of a wave fills 1 KB of LDS, lane l at byte 16 l:
-    // 16 stage rows (row 16 g + l / 4, physical segment l % 4, holding the
-    // logical segment (l % 4) ^ ((row >> 2) & 3) of the swizzled layout).
-    // The NG row groups of a stage are dealt to the waves round-robin; a wave
-    // with fewer groups repeats its last one (identical data to identical
-    // bytes), so that every wave issues GPW loads per stage and one
-    // immediate vmcnt fits all.  Points past the segment end and columns past
-    // N read a clamped (valid) row: their products are never stored.
-    constexpr int NG = ROWS / 16;
-    constexpr int GPW = (NG + NTH / 64 - 1) / (NTH / 64);
-    static_assert((NS - 2) * GPW <= 63, "outstanding loads exceed the vmcnt range");
+    // 16 rows of a slice (row 16 g + l / 4, physical segment l % 4, holding
+    // the logical segment (l % 4) ^ ((row >> 2) & 3) of the swizzled layout).
+    // The row groups of X and of the weights are dealt to the waves
+    // round-robin.  A group lies in one stream of X, or in the weights: its
+    // address is a wave-uniform base plus a 32-bit lane offset.  Points past
+    // the segment end and columns past N read a clamped (valid) row: their
+    // products are never stored.
+    constexpr int NW = NTH / 64;
+    constexpr int XG = C * BM / 16, WG = BN / 16;
+    constexpr int XPW = (XG + NW - 1) / NW, WPW = (WG + NW - 1) / NW;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const char* dsrc[GPW];
-    int dlds[GPW];
-    bool dx[GPW];
+    const int sgl = ((lane & 3) ^ ((lane >> 4) & 3)) * 16;   // the lane's logical segment (row >> 2 = lane >> 4 mod 4)
+    const char* xsrc[XPW];
+    uint32_t xoff[XPW];
+    const char* wsrc[WPW];
+    uint32_t woff[WPW];
 #pragma unroll
-    for (int i = 0; i < GPW; ++i) {
-      int grp = wv + i * (NTH / 64);
-      if (grp > NG - 1) grp = NG - 1;
-      dlds[i] = grp * 1024;
-      const int row = grp * 16 + (lane >> 2);
-      const int ls = (lane & 3) ^ ((row >> 2) & 3);
-      dx[i] = grp * 16 < C * BM;   // a 16-row group is all X rows or all weight rows (C * BM % 16 == 0)
-      if (row < C * BM) {
-        const int k = row / BM, pp = row % BM;
-        int64_t pt = m0 + pp;
-        if (pt > npts - 1) pt = npts - 1;
-        dsrc[i] = Xb + (p.seg.row0 + k * p.seg.plane + pt) * p.ldx * (int64_t)ES + ls * 16;
-      } else {
-        int n = n0 + row - C * BM;
-        if (n > p.N - 1) n = p.N - 1;
-        dsrc[i] = Wb + (int64_t)n * p.ldw * (int64_t)ES + ls * 16;
-      }
+    for (int i = 0; i < XPW; ++i) {
+      const int row0 = (wv + i * NW) * 16;
+      const int k = row0 / BM;
+      int64_t pp = row0 % BM + (lane >> 2);
+      if (pp > npts - 1 - m0) pp = npts - 1 - m0;
+      xsrc[i] = Xb + (p.seg.row0 + k * p.seg.plane + m0) * p.ldx * (int64_t)ES;
+      xoff[i] = (uint32_t)(pp * p.ldx * ES) + sgl;
     }
-    auto issue = [&](int kt, int stage) {
-      const int ktx = kxs(kt);
 #pragma unroll
-      for (int i = 0; i < GPW; ++i)
-        __builtin_amdgcn_global_load_lds((const void*)(dsrc[i] + (int64_t)(dx[i] ? ktx : kt) * 64),
-                                         (lds_ptr_t)(lds + stage * STAGE + dlds[i]), 16, 0, 0);
+    for (int i = 0; i < WPW; ++i) {
+      int n = (wv + i * NW) * 16 + (lane >> 2);
+      if (n > p.N - 1 - n0) n = p.N - 1 - n0;
+      wsrc[i] = Wb + (int64_t)n0 * p.ldw * (int64_t)ES;
+      woff[i] = (uint32_t)(n * p.ldw * ES) + sgl;
+    }
+    char* const xlds = lds;
+    char* const wlds = lds + 2 * XBUF;
+    // stages: k slice sx of X; TWO: weight stage s takes the low (s even) or
+    // the high terms of slice s / 2
+    const int nx = (TWO ? p.kx : p.K) / 64;
+    const int ns = TWO ? 2 * nx : nx;
+    auto issue = [&](int s) {
+      const int sx = TWO ? s >> 1 : s;
+      const int64_t wk = TWO ? (int64_t)sx * 128 + ((s & 1) ? 0 : p.kx * (int64_t)ES) : (int64_t)s * 128;
+#pragma unroll
+      for (int i = 0; i < WPW; ++i) {
+        if (WG % NW != 0 && wv + i * NW >= WG) break;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          __builtin_amdgcn_global_load_lds((const void*)(wsrc[i] + wk + 64 * h + woff[i]),
+                                           (lds_ptr_t)(wlds + (s & 1) * WBUF + h * (WBUF / 2) + (wv + i * NW) * 1024),
+                                           16, 0, 0);
+      }
+      if (TWO && (s & 1)) return;
+      // (read two stages apart with TWO: the slice's buffer was last read by stage s - 3)
+#pragma unroll
+      for (int i = 0; i < XPW; ++i) {
+        if (XG % NW != 0 && wv + i * NW >= XG) break;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          __builtin_amdgcn_global_load_lds((const void*)(xsrc[i] + (int64_t)sx * 128 + 64 * h + xoff[i]),
+                                           (lds_ptr_t)(xlds + (sx & 1) * XBUF + h * (XBUF / 2) + (wv + i * NW) * 1024),
+                                           16, 0, 0);
+      }
     };
+    frag xf[2][MT][C], wf[2][NT];
+    auto read_chunk = [&](int s, int c, int b) {
+      const char* xb = xlds + ((TWO ? s >> 1 : s) & 1) * XBUF + (c >> 1) * (XBUF / 2);
+      const char* wb = wlds + (s & 1) * WBUF + (c >> 1) * (WBUF / 2);
 #pragma unroll
-    for (int s = 0; s < NS - 1; ++s)
-      if (s < nk) issue(s, s);
-    int st = 0;
-    for (int kt = 0; kt < nk; ++kt) {
-      // own loads of stage kt complete: the later stages issued so far may
-      // still be in flight
-      const int later = nk - 1 - kt;
-      if constexpr (NS >= 4) {
-        if (later >= 2) wait_vmcnt<2 * GPW>();
-        else if (later == 1) wait_vmcnt<GPW>();
-        else wait_vmcnt<0>();
-      } else if constexpr (NS == 3) {
-        if (later >= 1) wait_vmcnt<GPW>();
-        else wait_vmcnt<0>();
-      } else {
-        wait_vmcnt<0>();
-      }
-      // every wave's loads of stage kt have landed, and every wave is done
-      // with stage kt - 1, whose buffer the next issue refills
+      for (int t = 0; t < NT; ++t) wf[b][t] = frag_at(wb, 32 * (wn * NT + t) + (lane & 31), c & 1);
+#pragma unroll
+      for (int u = 0; u < MT; ++u)
+#pragma unroll
+        for (int k = 0; k < C; ++k) xf[b][u][k] = frag_at(xb, k * BM + 32 * (MT * wm + u) + (lane & 31), c & 1);
+    };
+    auto products = [&](int b) {
+#pragma unroll
+      for (int u = 0; u < MT; ++u)
+#pragma unroll
+        for (int k = 0; k < C; ++k)
+#pragma unroll
+          for (int t = 0; t < NT; ++t) Elem<T>::mma(acc[u][k][t], wf[b][t], xf[b][u][k]);   // rows: columns n; cols: points
+    };
+    // PIPE (where the registers allow it): the fragments of a 16-wide chunk
+    // are read one chunk ahead of their products, across the stage barrier too
+    constexpr bool PIPE = MT * C * NT * 16 + 8 * (MT * C + NT) + (PRE ? 8 * MT * C * NT : 0) <= PIPE_REGS;
+    if constexpr (PIPE) {
+      issue(0);
+      wait_vmcnt<0>();
       lds_sync();
-      if (kt + NS - 1 < nk) issue(kt + NS - 1, st == 0 ? NS - 1 : st - 1);
-      if constexpr (PM == PM_F64) compute64(st); else compute(st);
-      fold();
-      st = st + 1 == NS ? 0 : st + 1;
+      if (ns > 1) issue(1);
+      read_chunk(0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      for (int s = 0; s < ns; ++s) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          read_chunk(s, c + 1, (c + 1) & 1);
+          __builtin_amdgcn_sched_barrier(0);
+          products(c & 1);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (s + 1 < ns) {
+          wait_vmcnt<0>();
+          lds_sync();   // stage s + 1 has landed for every wave, stage s has been read by every wave
+          if (s + 2 < ns) issue(s + 2);
+          read_chunk(s + 1, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        products(1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+      issue(0);
+      for (int s = 0; s < ns; ++s) {
+        wait_vmcnt<0>();
+        lds_sync();   // stage s has landed for every wave, and every wave is done with stage s - 1
+        if (s + 1 < ns) issue(s + 1);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          read_chunk(s, c, 0);
+          products(0);
+        }
+      }
     }
-    lds_sync();
   } else if constexpr (DB && NB > 2) {
     // two LDS stages and a ring of NB register buffers: buffer b holds the
     // stages kt = b (mod NB), so the global loads of stage kt + NB are issued
@@ -600,12 +794,9 @@ k_gemm_nt(const NtArgs<T> p) {
   // owns one point of each of its MT point sub-tiles and, in register group q
   // (regs 4q..4q+3), four consecutive columns 8q + 4*(lane >> 5) + 0..3 of
   // every 32x32 tile: all jet streams of a (point, column) sit in the same
-  // lane.  Results are staged through LDS one stream at a time and leave in
-  // full 16-byte row segments.
-  const int hh = lane >> 5;
-  auto mloc = [&](int u) { return 32 * (MT * wm + u) + (lane & 31); };            // point within the block
-  auto ncol = [&](int t, int q) { return 32 * (wn * NT + t) + 8 * q + 4 * hh; };   // column within the block
-
+  // lane.  Results leave straight from the registers as 16-byte row pieces
+  // (frag_store): staging every stream through LDS took two barriers per
+  // stream and array, which on the one-block-per-CU tiles nothing overlapped.
   if (EPI == EPI_DF) {
     const int64_t ldY = p.sY_ld > 0 ? p.sY_ld : p.nY, ldU = p.sU_ld > 0 ? p.sU_ld : p.nU;
 #pragma unroll
@@ -627,83 +818,69 @@ k_gemm_nt(const NtArgs<T> p) {
     return;
   }
 
-  // adds a [points x columns] array of every stream (rows laid out as the
-  // outputs) to the accumulators: residual skips of a shared trunk
-  auto add_rows = [&](const T* src) {
+  // writes / adds a [points x columns] array of every stream, laid out as the
+  // outputs (N is a multiple of 32 here: a fragment's columns are all valid or
+  // none)
+  auto store_rows = [&](T* dst, int u, int t) {
+    if (fcol(t) >= p.N) return;
+    const int64_t p0 = fpt(u, 0), p1 = fpt(u, 1);
 #pragma unroll
-    for (int u = 0; u < MT; ++u) {
-      const int64_t pt = m0 + mloc(u);
-      const bool pvalid = pt < npts;
+    for (int k = 0; k < C; ++k) {
+      FragRaw<T> f;
+      frag_pack<T>(f, acc[u][k][t]);
+      T* row = dst + g * p.o_g + (p.seg.row0 + k * p.seg.plane + p0) * p.ldo + fcol(t);
 #pragma unroll
-      for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int nb = n0 + ncol(t, q);
-          if (!pvalid || nb >= p.N) continue;
-#pragma unroll
-          for (int k = 0; k < C; ++k) {
-            float v[4];
-            load4<T>(src + g * p.o_g + (p.seg.row0 + k * p.seg.plane + pt) * p.ldo + nb, v);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[u][k][t][4 * q + e] += v[e];
-          }
-        }
+      for (int i = 0; i < (ES == 2 ? 1 : 2); ++i) {
+        if (p0 < npts) *(u32x4*)(row + frag_col<T>(lane, i)) = f.w[i][0];
+        if (p1 < npts) *(u32x4*)(row + 16 * p.ldo + frag_col<T>(lane, i)) = f.w[i][1];
+      }
     }
   };
-
-  // staging: one [BM x BN] plane at a time through LDS, copied out in full
-  // 16-byte row segments
-  constexpr int CPR = BN * ES / 16;                // 16-byte chunks per staged row
-  constexpr int CHUNKS = BM * CPR;
-  auto stage_out = [&](int k, T* dst) {
+  auto load_rows = [&](FragRaw<T>* raw, const T* src, int u, int t) {
 #pragma unroll
-    for (int u = 0; u < MT; ++u)
+    for (int k = 0; k < C; ++k) load_frag(raw[k], src, u, k, t);
+    __builtin_amdgcn_sched_barrier(0);   // all in flight together
+  };
+  auto add_rows = [&](FragRaw<T>* raw, int u, int t) {
 #pragma unroll
-      for (int t = 0; t < NT; ++t)
+    for (int k = 0; k < C; ++k) {
+      frag_unswap<T>(raw[k]);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          float v[4];
+      for (int q = 0; q < 4; ++q) {
+        float v[4];
+        frag_group<T>(raw[k], q, v);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = acc[u][k][t][4 * q + e];
-          store4<T>((T*)(lds + mloc(u) * OPITCH + ncol(t, q) * ES), v);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-    lds_sync();
-#pragma unroll
-    for (int it = 0; it < (CHUNKS + NTH - 1) / NTH; ++it) {
-      const int i = tid + it * NTH;
-      if (CHUNKS % NTH != 0 && i >= CHUNKS) break;
-      const int row = i / CPR, ch = i % CPR;
-      const int64_t ptr = m0 + row;
-      const int n = n0 + ch * (16 / ES);
-      if (ptr < npts && n < p.N)
-        *(uint4*)(dst + g * p.o_g + (p.seg.row0 + k * p.seg.plane + ptr) * p.ldo + n) =
-            *(const uint4*)(lds + row * OPITCH + ch * 16);
+        for (int e = 0; e < 4; ++e) acc[u][k][t][4 * q + e] += v[e];
+      }
     }
-    lds_sync();
   };
 
   if (EPI == EPI_FWD) {
     // pre-activations (bias on the value stream), then activations in place:
     //   h = t, h'_i = s a'_i, h''_i = s a''_i + s' (a'_i)^2
+    // (all biases of a lane are read together: behind a check of its own, each
+    // of the up to 32 loads was waited for by itself, about a third of a
+    // block's time at K = 512)
 #pragma unroll
-    for (int u = 0; u < MT; ++u)
+    for (int t = 0; t < NT; ++t) {
+      float bv[16];
+      {
+        // columns past N take the first biases (their results are never stored)
+        const float* bp = p.bias + g * p.b_g + (fcol(t) < p.N ? fcol(t) : 0) + 4 * hh;
 #pragma unroll
-      for (int t = 0; t < NT; ++t)
+        for (int r = 0; r < 16; ++r) bv[r] = bp[8 * (r >> 2) + (r & 3)];
+      }
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          // columns past N take the last bias (their results are never stored)
-          const int n = n0 + ncol(t, r >> 2) + (r & 3);
-          if (p.bias) acc[u][0][t][r] += p.bias[g * p.b_g + (n < p.N ? n : p.N - 1)];
+      for (int u = 0; u < MT; ++u) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[u][0][t][r] += bv[r];
+        // (the residual rows are read ahead of the tanh where they fit)
+        constexpr bool AHEAD = MT * C * NT * 16 < 160;
+        FragRaw<T> sk[AHEAD ? C : 1];
+        if constexpr (AHEAD) {
+          if (p.skip) load_rows(sk, p.skip, u, t);
         }
-    if (p.out_a) {
-#pragma unroll
-      for (int k = 0; k < C; ++k) stage_out(k, p.out_a);
-    }
-#pragma unroll
-    for (int u = 0; u < MT; ++u)
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
+        if (p.out_a) store_rows(p.out_a, u, t);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           float v[C];
@@ -712,77 +889,74 @@ k_gemm_nt(const NtArgs<T> p) {
           jet_fwd<ND1, ND2, X64>(v);
 #pragma unroll
           for (int k = 0; k < C; ++k) acc[u][k][t][r] = v[k];
+          if (MT * C * NT * 16 >= 160 && r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
-    // residual block output: h_l = tanh carry + h_{l-2}, stream by stream
-    if (p.skip) add_rows(p.skip);
-#pragma unroll
-    for (int k = 0; k < C; ++k) stage_out(k, p.out_h);
+        // residual block output: h_l = tanh carry + h_{l-2}, stream by stream
+        if (p.skip) {
+          if constexpr (AHEAD) {
+            add_rows(sk, u, t);
+          } else {
+            FragRaw<T> late[C];
+            load_rows(late, p.skip, u, t);
+            add_rows(late, u, t);
+          }
+        }
+        store_rows(p.out_h, u, t);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
     return;
   }
 
-  // skip cotangent of a residual block's input, and the total kept for the
-  // skip below it
-  if (p.skip_g) add_rows(p.skip_g);
-  if (p.out_gh) {
-#pragma unroll
-    for (int k = 0; k < C; ++k) stage_out(k, p.out_gh);
-  }
-
-  // reverse carry, in place: acc[k] becomes the cotangent of the saved
-  // pre-activation a_k of the layer below
+  // reverse pass: the skip cotangent of a residual block's input, the total
+  // kept for the skip below it, then the reverse carry in place: acc[k]
+  // becomes the cotangent of the saved pre-activation a_k of the layer below
 #pragma unroll
   for (int u = 0; u < MT; ++u) {
-    // points past the segment end and columns past N read a clamped (valid)
-    // element: their results are never stored, and unconditional loads keep
-    // the loads of a fragment together, without a branch around each
-    int64_t pt = m0 + mloc(u);
-    if (pt > npts - 1) pt = npts - 1;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      // the saved pre-activations of all four column groups of this fragment,
-      // issued together (one memory latency per fragment, not per group)
-      typedef typename std::conditional<ES == 2, uint2, float4>::type raw_t;
-      raw_t raw[4][C];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        int nb = n0 + ncol(t, q);
-        if (nb >= p.N) nb = 0;
-#pragma unroll
-        for (int k = 0; k < C; ++k)
-          raw[q][k] = *(const raw_t*)(p.aprev + g * p.o_g + (p.seg.row0 + k * p.seg.plane + pt) * p.ldo + nb);
+      if (p.skip_g) {
+        FragRaw<T> sk[C];
+        load_rows(sk, p.skip_g, u, t);
+        add_rows(sk, u, t);
       }
+      FragRaw<T> raw[PRE ? 1 : C];
+      if constexpr (!PRE) load_rows(raw, p.aprev, u, t);
+      if (p.out_gh) store_rows(p.out_gh, u, t);
+#pragma unroll
+      for (int k = 0; k < C; ++k) {
+        if constexpr (PRE) frag_unswap<T>(apre[u][k][t]);
+        else frag_unswap<T>(raw[k]);
+      }
+      // a register group at a time (all of a fragment would spill beside the
+      // accumulators of the larger tiles)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         float ap[C][4];
 #pragma unroll
         for (int k = 0; k < C; ++k) {
-          if constexpr (ES == 2) {
-            const T* ev = (const T*)&raw[q][k];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) ap[k][e] = Elem<T>::to_f(ev[e]);
-          } else {
-            ap[k][0] = raw[q][k].x; ap[k][1] = raw[q][k].y; ap[k][2] = raw[q][k].z; ap[k][3] = raw[q][k].w;
-          }
+          if constexpr (PRE) frag_group<T>(apre[u][k][t], q, ap[k]);
+          else frag_group<T>(raw[k], q, ap[k]);
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const int r = 4 * q + e;
           float gv[C], av[C];
 #pragma unroll
           for (int k = 0; k < C; ++k) {
-            gv[k] = acc[u][k][t][r];
+            gv[k] = acc[u][k][t][4 * q + e];
             av[k] = ap[k][e];
           }
           jet_bwd<ND1, ND2, X64>(gv, av);
 #pragma unroll
-          for (int k = 0; k < C; ++k) acc[u][k][t][r] = gv[k];
+          for (int k = 0; k < C; ++k) acc[u][k][t][4 * q + e] = gv[k];
+          if (X64 && e % 2 == 1) __builtin_amdgcn_sched_barrier(0);
         }
+        if (X64 || MT * C * NT * 16 >= 112 || q % 2 == 1) __builtin_amdgcn_sched_barrier(0);
       }
+      store_rows(p.out_da, u, t);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-#pragma unroll
-  for (int k = 0; k < C; ++k) stage_out(k, p.out_da);
 }
 
 // ---------------------------------------------------------------------------
@@ -1964,8 +2138,15 @@ int cu_count() {
   return cached[dev];
 }
 
-template <class T, int C>
-constexpr bool wide_ok() { return sizeof(T) == 2 && (C == 1 || C == 3 || C == 5); }
+// launches of the ring kernels: whole 128-byte k slices, and the arrays' rows
+// addressable from a tile's first row with 32-bit offsets (a tile spans at
+// most 256 rows)
+template <class T, int C, int EPI>
+bool ring_ok(const NtArgs<T>& a) {
+  const int kx = a.kx > 0 ? a.kx : a.K;
+  return sizeof(T) == 2 && EPI != EPI_DF && !(EPI == EPI_BWD && C == 1) && (EPI == EPI_FWD) == (a.kx > 0) && a.N >= 128 &&
+         kx >= 128 && kx % 64 == 0 && a.ldx < (1 << 22) && a.ldw < (1 << 22);
+}
 
 template <class T, int ND1, int ND2, int EPI>
 hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
@@ -1973,6 +2154,7 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
   constexpr int NTM = C == 1 ? 4 : (C == 2 ? 2 : 1);
   const int64_t npts = a.seg.n_points;
   if (npts <= 0) return hipSuccess;
+  if (EPI == EPI_FWD && !a.bias) return hipErrorInvalidValue;
   if ((a.pm != PM_NATIVE && sizeof(T) != 4) || (a.kx > 0 && (sizeof(T) != 2 || a.K != 2 * a.kx)))
     return hipErrorInvalidValue;
   if constexpr (sizeof(T) == 4) {
@@ -2054,64 +2236,39 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
   if (a.N <= 32) {
     dim3 grid((unsigned)(((npts + 127) / 128) * ((a.N + 31) / 32)), 1, G);
     k_gemm_nt<T, ND1, ND2, 4, 1, 1, 1, EPI, (C >= 4 ? 1 : 2)><<<grid, 256, 0, st>>>(a);
-  } else if (wide_ok<T, C>() && a.K >= 256 && a.N >= 256) {
-    // wide layers: operand stages loaded straight into an LDS ring several
-    // stages ahead, larger wave tiles (fewer LDS fragment reads per MFMA) and
-    // fewer L2 re-reads of each activation tile.  Tile shapes are the
-    // fastest measured per stream count, epilogue and depth (K = 256 layers
-    // are bound by HBM traffic, K >= 512 by the matrix cores).
-    const bool deep = a.K >= 512;
-    if constexpr (!wide_ok<T, C>()) {
-      return hipErrorInvalidValue;
-    } else if constexpr (C == 1) {
-      if constexpr (EPI == EPI_BWD) {
-        if (deep) {
-          // 128 points x 256 columns, 2 x 4 fragments per wave, 3-stage ring
-          dim3 grid((unsigned)(((npts + 127) / 128) * ((a.N + 255) / 256)), 1, G);
-          k_gemm_nt<T, ND1, ND2, 2, 2, 2, 4, EPI, 2, true, 3><<<grid, 256, 0, st>>>(a);
+  } else if (ring_ok<T, C, EPI>(a)) {
+    // 16-bit layers of 128 columns and more (128 itself: what the resident
+    // kernel does not take): operand stages straight into LDS.  Large tiles
+    // read every operand fewer times and suit the matrix-core-bound depths;
+    // 32 points x 128 columns (four waves, two blocks per CU for up to five
+    // streams, so that one block's epilogue runs beside the other's products)
+    // suits launches that would give the chip fewer than two rounds of large
+    // tiles, five streams at K = 256 (HBM-bound) and every reverse pass of
+    // five streams.  us per launch, K = N = 256 / 512 (262,144 points) / 1024
+    // (131,072), before -> now (large tile | 32 x 128):
+    //   forward  C = 5:  737 / 1812 / 2977 ->  651 / 1637 / 2619 |  599 / 1755 / 2930
+    //            C = 3:  436 / 1205 / 1986 ->  404 / 1020 / 1690 |  425 / 1210 / 2118
+    //            C = 1:  719 / 2080 / 3251 ->  545 / 1492 / 2317 (4 x the points)
+    //   reverse  C = 5:  554 / 1425 / 2152 ->  568 / 1446 / 2022 |  480 / 1217 / 1869
+    //            C = 3:    - /  862 / 1242 ->  330 /  772 / 1109 |  318 /  881 / 1312
+    if constexpr (sizeof(T) == 2 && EPI != EPI_DF && !(EPI == EPI_BWD && C == 1)) {
+      constexpr bool TWO = EPI == EPI_FWD;
+      constexpr int WM = C == 1 ? 4 : 2, WN = C == 1 ? 2 : 4, MT = C <= 3 && TWO ? 2 : 1, NT = C == 1 ? 4 : (C <= 3 || C == 5 ? 2 : 1);
+      constexpr int BM = 32 * MT * WM, BN = 32 * NT * WN;
+      const int64_t blocks = ((npts + BM - 1) / BM) * ((a.N + BN - 1) / BN) * G;
+      const bool large = a.N >= 256 && blocks >= 2 * (int64_t)cu_count() && !(C == 5 && (!TWO || a.N == 256)) &&
+                         !(C == 3 && !TWO && a.N == 256);
+      if constexpr (TWO || C <= 4) {
+        if (large) {
+          dim3 grid((unsigned)(((npts + BM - 1) / BM) * ((a.N + BN - 1) / BN)), 1, G);
+          k_gemm_nt<T, ND1, ND2, WM, WN, MT, NT, EPI, 1, true, true, PM_NATIVE, 2, TWO><<<grid, 64 * WM * WN, 0, st>>>(a);
           return hipGetLastError();
         }
       }
-      if (((npts + 127) / 128) * ((a.N + 127) / 128) * G < 64) {
-        // short launches (a critic's batch): 32 points x 128 columns, four
-        // waves of one fragment, for four times the blocks
-        dim3 grid((unsigned)(((npts + 31) / 32) * ((a.N + 127) / 128)), 1, G);
-        k_gemm_nt<T, ND1, ND2, 1, 4, 1, 1, EPI, 2, true, 3><<<grid, 256, 0, st>>>(a);
-      } else {
-        // 128 points x 128 columns, 2 x 2 fragments per wave, 3-stage ring
-        dim3 grid((unsigned)(((npts + 127) / 128) * ((a.N + 127) / 128)), 1, G);
-        k_gemm_nt<T, ND1, ND2, 2, 2, 2, 2, EPI, 2, true, 3><<<grid, 256, 0, st>>>(a);
-      }
-    } else if constexpr ((C == 5 || C == 3) && EPI == EPI_BWD) {
-      if constexpr (C == 3) {
-        if (deep) {
-          // eight waves (2 x 4), 64 points x 256 columns, 3-stage ring
-          dim3 grid((unsigned)(((npts + 63) / 64) * ((a.N + 255) / 256)), 1, G);
-          k_gemm_nt<T, ND1, ND2, 2, 4, 1, 2, EPI, 1, false, 3><<<grid, 512, 0, st>>>(a);
-          return hipGetLastError();
-        }
-      }
-      // four waves (1 x 4), 32 points x 128 columns, 3-stage ring: two blocks
-      // per CU, so that one block's epilogue (the jet carry, VALU work a third
-      // to three quarters as long as its products) runs beside the other's
-      // products (five streams: 8-10 % faster than eight waves of 32 x 256 or
-      // 64 x 128 at K = 1024 and 256; three streams at K = 256: 15 % faster
-      // than the register-staged 64 x 128 tile)
       dim3 grid((unsigned)(((npts + 31) / 32) * ((a.N + 127) / 128)), 1, G);
-      k_gemm_nt<T, ND1, ND2, 1, 4, 1, 1, EPI, 2, true, 3><<<grid, 256, 0, st>>>(a);
+      k_gemm_nt<T, ND1, ND2, 1, 4, 1, 1, EPI, (C <= 5 ? 2 : 1), true, true, PM_NATIVE, 2, TWO><<<grid, 256, 0, st>>>(a);
     } else {
-      if constexpr (C == 3 && EPI == EPI_FWD) {
-        if (!deep) {
-          // eight waves (2 x 4), 64 points x 128 columns, 4-stage ring
-          dim3 grid((unsigned)(((npts + 63) / 64) * ((a.N + 127) / 128)), 1, G);
-          k_gemm_nt<T, ND1, ND2, 2, 4, 1, 1, EPI, 2, true, 4><<<grid, 512, 0, st>>>(a);
-          return hipGetLastError();
-        }
-      }
-      // eight waves (2 x 4), 64 points x 256 columns, 3-stage ring (6-11 %
-      // faster than 4 stages at K = 1024, two-term forward and reverse)
-      dim3 grid((unsigned)(((npts + 63) / 64) * ((a.N + 255) / 256)), 1, G);
-      k_gemm_nt<T, ND1, ND2, 2, 4, 1, 2, EPI, 1, false, 3><<<grid, 512, 0, st>>>(a);
+      return hipErrorInvalidValue;
     }
   } else {
     constexpr int BN = 64 * NTM;
