@@ -151,10 +151,13 @@ static pigan_status check_dtype(int32_t dt) {
   return PIGAN_OK;
 }
 
-// row chunks per sample of the first-layer reverse pass: about 1024 blocks
-static int first_bwd_chunks(int S) {
-  int c = (1024 + S - 1) / S;
-  return c < 1 ? 1 : (c > 64 ? 64 : c);
+// row chunks per sample of the first-layer reverse pass: about 1024 blocks,
+// each with at least four passes of its threads (256 / (W / 8) points a pass):
+// shorter chunks only add partials
+static int first_bwd_chunks(int S, int64_t points, int W) {
+  const int64_t per_pass = std::max(1, 256 / (W / 8));
+  const int64_t c = std::min<int64_t>((1024 + S - 1) / S, points / (4 * per_pass));
+  return (int)(c < 1 ? 1 : (c > 64 ? 64 : c));
 }
 
 // points per block of the output-layer reverse pass: about 2048 blocks for
@@ -294,7 +297,7 @@ static void plan_net(Carver& cv, NetBuf& nb, const pigan_mlp& m, int d, int nd2,
   nb.wcT = cv.take(nw * es);
   nb.ws = cv.take(nw * 4);
   nb.wsT = cv.take(nw * 4);
-  nb.nrc = first_bwd_chunks(Sc);
+  nb.nrc = first_bwd_chunks(Sc, (int64_t)P + n_s, W);
   nb.fb = cv.take((size_t)Sc * nb.nrc * 7 * W * 8 * G);
   nb.ppb_sen = ob_ppb(nb.n_sen, W);
   nb.ppb_col = ob_ppb(nb.n_col, W);

@@ -822,11 +822,18 @@ k_colsum(const Tin* __restrict__ part, int64_t p_g, int n_slots, int64_t slot_st
 //   q=0   : dA_1 over value rows                       (gs)
 //   q=1..3: dA_1 * x_i over value rows                  (gx_i)
 //   q=4..6: dA_1 over the d/dx_i rows                   (gd_i; a'_i = W1[:, i])
-// into part[g][s][rc][q][n] (fp32; slots beyond d stay zero).
+// into part[g][s][rc][q][n] (fp64; only the sums of the D coordinates).
+// A thread owns 8 columns; TPP = min(W / 8, 256) threads share a point, 256 /
+// TPP points per pass.  The point lanes of a wave are summed by shuffles, the
+// waves through LDS: summed by the first TPP threads alone, one LDS read
+// after another, that tail took most of the kernel for narrow layers (W = 32,
+// 64 samples of 32 + 8 points: 123 us; W = 128, 256 samples of 1024 + 200: 112
+// us).
 // ---------------------------------------------------------------------------
-template <class T>
+template <class T, int D>
 __global__ void __launch_bounds__(256)
 k_first_bwd(FirstBwdArgs<T> p) {
+  constexpr int NQ = 1 + 2 * D;                    // sums: 0, 1..D, 4..3+D
   __shared__ double red[256 * 8];
   const int g = blockIdx.z;
   const int s = blockIdx.x / p.nrc;
@@ -838,71 +845,80 @@ k_first_bwd(FirstBwdArgs<T> p) {
   const int lt = threadIdx.x % TPP;
   const int lp = threadIdx.x / TPP;
   const int cg = blockIdx.y * 256 + lt;
-  const bool valid = cg < G8;
+  const bool valid = cg < G8 && lp < PPP;          // (256 may leave a part of a point's threads over)
   const int n0 = cg * 8;
-  const int d = p.d;
-  double acc[7][8];
+  double acc[NQ][8];
 #pragma unroll
-  for (int q = 0; q < 7; ++q)
+  for (int q = 0; q < NQ; ++q)
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[q][e] = 0.0;
   const T* A = p.dA + g * p.a_g;
   if (valid) {
     const int j0 = (int)((int64_t)p.n_s * rc / p.nrc), j1 = (int)((int64_t)p.n_s * (rc + 1) / p.nrc);
     const float* As = p.dAs + g * p.as_g;
+#pragma unroll 2
     for (int j = j0 + lp; j < j1; j += PPP) {
       float v[8];
       load8<float>(As + ((int64_t)s * p.n_s + j) * p.ldas + n0, v);
-      const float* xv = p.xs + g * p.xs_g + (int64_t)j * d;
-      double x[3];
+      const float* xv = p.xs + g * p.xs_g + (int64_t)j * D;
+      double x[D];
 #pragma unroll
-      for (int i = 0; i < 3; ++i) x[i] = i < d ? (double)xv[i] : 0.0;
+      for (int i = 0; i < D; ++i) x[i] = (double)xv[i];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         acc[0][e] += (double)v[e];
 #pragma unroll
-        for (int i = 0; i < 3; ++i) acc[1 + i][e] += (double)v[e] * x[i];
+        for (int i = 0; i < D; ++i) acc[1 + i][e] += (double)v[e] * x[i];
       }
     }
     const int q0 = (int)((int64_t)p.P * rc / p.nrc), q1 = (int)((int64_t)p.P * (rc + 1) / p.nrc);
 #pragma unroll 4
     for (int q = q0 + lp; q < q1; q += PPP) {
       const int64_t pt = (int64_t)s * p.P + q;
-      float v[8];
+      float v[8], u[D][8];
       load8<T>(A + pt * p.lda + n0, v);
-      const float* xv = p.xc + g * p.xc_g + pt * d;
-      float x[3];
 #pragma unroll
-      for (int i = 0; i < 3; ++i) x[i] = i < d ? xv[i] : 0.0f;
+      for (int i = 0; i < D; ++i) load8<T>(A + ((1 + i) * p.n_col + pt) * p.lda + n0, u[i]);
+      const float* xv = p.xc + g * p.xc_g + pt * D;
+      float x[D];
+#pragma unroll
+      for (int i = 0; i < D; ++i) x[i] = xv[i];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         acc[0][e] += (double)v[e];
 #pragma unroll
-        for (int i = 0; i < 3; ++i) acc[1 + i][e] += (double)(v[e] * x[i]);
-      }
-#pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        if (i >= p.nd1) continue;
-        float u[8];
-        load8<T>(A + ((1 + i) * p.n_col + pt) * p.lda + n0, u);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[4 + i][e] += (double)u[e];
+        for (int i = 0; i < D; ++i) {
+          acc[1 + i][e] += (double)(v[e] * x[i]);
+          acc[1 + D + i][e] += (double)u[i][e];
+        }
       }
     }
   }
+  // point lanes of a wave (a wave holds 64 / TPP points when TPP < 64)
+  for (int off = TPP; off < 64; off <<= 1) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[q][e] += __shfl_xor(acc[q][e], off);
+  }
+  // waves: PW of them hold sums of the same columns
+  const int lanes = TPP < 64 ? TPP : 64;
+  const int PW = TPP < 64 ? 4 : PPP;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int grp = TPP < 64 ? wave : lp;            // which of the PW sums this thread holds
   double* out = p.part + (((int64_t)g * p.S + s) * p.nrc + rc) * 7 * W;
 #pragma unroll
-  for (int q = 0; q < 7; ++q) {
+  for (int q = 0; q < NQ; ++q) {
+    if (lane < lanes && lp < PPP) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) red[threadIdx.x * 8 + e] = acc[q][e];
+      for (int e = 0; e < 8; ++e) red[(grp * 8 + e) * TPP + lt] = acc[q][e];
+    }
     __syncthreads();
-    if (lp == 0 && valid) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        double t = 0.0;
-        for (int u = 0; u < PPP; ++u) t += red[(u * TPP + lt) * 8 + e];
-        out[(int64_t)q * W + n0 + e] = t;
-      }
+    for (int c = threadIdx.x; c < 8 * TPP; c += 256) {
+      const int n = blockIdx.y * 2048 + c;
+      double t = 0.0;
+      for (int u = 0; u < PW; ++u) t += red[(u * 8 + (c & 7)) * TPP + (c >> 3)];
+      if (n < W) out[(int64_t)(q <= D ? q : 3 + q - D) * W + n] = t;
     }
     __syncthreads();
   }
@@ -926,15 +942,14 @@ k_first_wgrad(const double* __restrict__ part, int S, int nrc, int W, int d, int
     const bool xcol = c < d;                       // weight of coordinate c: sum of gx_c and gd_c
     const bool two = xcol && c < nd1;
     const int64_t o1 = xcol ? (int64_t)(1 + c) * W : 0, o2 = (int64_t)(4 + c) * W;
-    for (int s = grp; s < S; s += 32) {
-      const double* b = pp + (int64_t)s * nrc * 7 * W;
-      double t = 0.0;
-#pragma unroll 4
-      for (int r = 0; r < nrc; ++r) {
-        t += b[(int64_t)r * 7 * W + o1];
-        if (two) t += b[(int64_t)r * 7 * W + o2];
-      }
-      if (!xcol && c < in_dim) t *= (double)z[g * z_g + (int64_t)s * n_z + (c - d)];
+    const bool zcol = !xcol && c < in_dim;
+    const int SR = S * nrc;
+#pragma unroll 8
+    for (int i = grp; i < SR; i += 32) {           // (eight independent loads in flight)
+      const double* b = pp + (int64_t)i * 7 * W;
+      double t = b[o1];
+      if (two) t += b[o2];
+      if (zcol) t *= (double)z[g * z_g + (int64_t)(i / nrc) * n_z + (c - d)];
       acc += t;
     }
   }
@@ -1329,7 +1344,10 @@ template <class T>
 hipError_t launch_first_bwd(const FirstBwdArgs<T>& a, int G, hipStream_t st) {
   if (a.S <= 0) return hipSuccess;
   dim3 grid(a.S * a.nrc, nblk(a.W / 8, 256), G);
-  k_first_bwd<T><<<grid, 256, 0, st>>>(a);
+  if (a.nd1 != a.d) return hipErrorInvalidValue;
+  if (a.d == 1) k_first_bwd<T, 1><<<grid, 256, 0, st>>>(a);
+  else if (a.d == 2) k_first_bwd<T, 2><<<grid, 256, 0, st>>>(a);
+  else k_first_bwd<T, 3><<<grid, 256, 0, st>>>(a);
   return hipGetLastError();
 }
 
