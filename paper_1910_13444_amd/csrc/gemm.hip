@@ -960,6 +960,339 @@ k_gemm_nt(const NtArgs<T> p) {
 }
 
 // ---------------------------------------------------------------------------
+// k_gemm_short: the fp64 products and epilogues of k_gemm_nt (fp32 storage)
+// where a launch has few output tiles: a critic's batch, small sensor sets.
+// There the tiled kernel is a serial chain of K stages on a few blocks (512
+// rows, N = 256, K = 416: 32 blocks, 26 stages, 26.6 us; here 10.6).  A block owns 32 points x 32 columns and its NW waves share the
+// contraction: each reads the operand fragments of its 16-wide chunks straight
+// from global memory into registers, two chunks ahead, and the fp64 partial
+// sums meet in LDS (added in wave order, rounded once).  The epilogue runs on
+// 256 threads, four consecutive columns of one point each.
+// ---------------------------------------------------------------------------
+template <int ND1, int EPI, int NW>
+__global__ void __launch_bounds__(64 * NW) k_gemm_short(const NtArgs<float> p) {
+  constexpr int C = 1 + ND1;
+  constexpr int SU = 2;                            // chunks in flight besides the ones being multiplied
+  constexpr int PITCH = 34;                        // of one point's 32 columns
+  __shared__ __attribute__((aligned(16))) double part[NW][32 * PITCH];
+  const int g = blockIdx.z;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ntn = p.N / 32;
+  const int64_t lt = xcd_remap(blockIdx.x, gridDim.x);
+  const int64_t m0 = (lt / ntn) * 32;
+  const int n0 = (int)(lt % ntn) * 32;
+  const int64_t npts = p.seg.n_points;
+  const int nch = p.K / 16;
+  const int c0 = (int)((int64_t)nch * wave / NW), c1 = (int)((int64_t)nch * (wave + 1) / NW);
+
+  // points past the end read the last one (their results are never stored)
+  auto xrow = [&](int r, int k) {
+    int64_t pt = m0 + r;
+    if (pt > npts - 1) pt = npts - 1;
+    return p.X + g * p.x_g + (p.seg.row0 + k * p.seg.plane + pt) * p.ldx;
+  };
+  f64x4 accd[C][2][2];
+#pragma unroll
+  for (int k = 0; k < C; ++k)
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) accd[k][a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+
+  {
+    // lane: row l & 15 of each 16-row half, four k values 4 (l >> 4) of a
+    // chunk; step j multiplies element j of every lane (both operands in the
+    // same k order)
+    const float* wr[2];
+    const float* xr[C][2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      wr[h] = p.Wm + g * p.w_g + (int64_t)(n0 + 16 * h + (lane & 15)) * p.ldw + 4 * (lane >> 4);
+#pragma unroll
+      for (int k = 0; k < C; ++k) xr[k][h] = xrow(16 * h + (lane & 15), k) + 4 * (lane >> 4);
+    }
+    f32x4 wb[2][SU][2], xb[2][SU][C][2];
+    auto load = [&](int b, int c) {
+#pragma unroll
+      for (int i = 0; i < SU; ++i) {
+        const int cc = c + i < c1 ? c + i : c1 - 1;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          wb[b][i][h] = *(const f32x4*)(wr[h] + cc * 16);
+#pragma unroll
+          for (int k = 0; k < C; ++k) xb[b][i][k][h] = *(const f32x4*)(xr[k][h] + cc * 16);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto mul = [&](int b, int c) {
+#pragma unroll
+      for (int i = 0; i < SU; ++i) {
+        if (c + i >= c1) break;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int k = 0; k < C; ++k)
+#pragma unroll
+            for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+              for (int nb = 0; nb < 2; ++nb)
+                accd[k][nb][pb] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)wb[b][i][nb][j], (double)xb[b][i][k][pb][j],
+                                                                       accd[k][nb][pb], 0, 0, 0);
+      }
+    };
+    if (c0 < c1) {
+      load(0, c0);
+      for (int c = c0; c < c1; c += 2 * SU) {
+        load(1, c + SU < c1 ? c + SU : c1 - 1);
+        mul(0, c);
+        if (c + SU >= c1) break;
+        load(0, c + 2 * SU < c1 ? c + 2 * SU : c1 - 1);
+        mul(1, c + SU);
+      }
+    }
+  }
+  // sums over the waves, one stream after the other
+  const int row = tid >> 3, cq = 4 * (tid & 7);     // threads 0..255: point, first column
+  float v[C][4];
+#pragma unroll
+  for (int k = 0; k < C; ++k) {
+    double* pw = part[wave];
+    if (k > 0) __syncthreads();                      // the previous stream has been summed
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int pb = 0; pb < 2; ++pb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          pw[(16 * pb + (lane & 15)) * PITCH + 16 * nb + (lane >> 4) + 4 * r] = accd[k][nb][pb][r];
+    __syncthreads();
+    if (tid < 256) {
+      double t[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int w = 0; w < NW; ++w)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] += part[w][row * PITCH + cq + e];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[k][e] = (float)t[e];
+    }
+  }
+  const int64_t pt = m0 + row;
+  if (tid >= 256 || pt >= npts) return;
+  const int n = n0 + cq;
+  if constexpr (EPI == EPI_DF) {
+    const int64_t ldY = p.sY_ld > 0 ? p.sY_ld : p.nY, ldU = p.sU_ld > 0 ? p.sU_ld : p.nU;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float o = p.df_sign * v[0][e];
+      if (n + e < p.nY) p.seedY[g * p.sY_g + pt * ldY + n + e] = o;
+      else if (n + e < p.nY + p.nU) p.seedU[g * p.sU_g + pt * ldU + p.sU_off + (n + e - p.nY)] = o;
+    }
+    return;
+  } else {
+    auto at = [&](auto* base, int k) { return base + g * p.o_g + (p.seg.row0 + k * p.seg.plane + pt) * p.ldo + n; };
+    auto put = [&](float* dst) {
+#pragma unroll
+      for (int k = 0; k < C; ++k) store4<float>(at(dst, k), v[k]);
+    };
+    auto add = [&](const float* src) {
+#pragma unroll
+      for (int k = 0; k < C; ++k) {
+        float s4[4];
+        load4<float>(at(src, k), s4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[k][e] += s4[e];
+      }
+    };
+    if constexpr (EPI == EPI_FWD) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[0][e] += p.bias[g * p.b_g + n + e];
+      if (p.out_a) put(p.out_a);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float x[C];
+#pragma unroll
+        for (int k = 0; k < C; ++k) x[k] = v[k][e];
+        jet_fwd<ND1, 0, true>(x);
+#pragma unroll
+        for (int k = 0; k < C; ++k) v[k][e] = x[k];
+      }
+      if (p.skip) add(p.skip);
+      put(p.out_h);
+    } else {
+      if (p.skip_g) add(p.skip_g);
+      if (p.out_gh) put(p.out_gh);
+      float ap[C][4];
+#pragma unroll
+      for (int k = 0; k < C; ++k) load4<float>(at(p.aprev, k), ap[k]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float gv[C], av[C];
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+          gv[k] = v[k][e];
+          av[k] = ap[k][e];
+        }
+        jet_bwd<ND1, 0, true>(gv, av);
+#pragma unroll
+        for (int k = 0; k < C; ++k) v[k][e] = gv[k];
+      }
+      put(p.out_da);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// k_gemm_short_x2: the split products (PM_SPLIT2) of k_gemm_nt where a launch
+// has few output tiles.  One wave per 32 points x 32 columns walks the
+// contraction in k_gemm_nt's order (so the results are the same bits), with
+// SU 16-wide chunks of operands in registers and as many on their way: no LDS,
+// no barrier, and 32 times as many waves in flight as blocks of the 64 x 256
+// tile.
+// ---------------------------------------------------------------------------
+template <int ND1, int EPI>
+__global__ void __launch_bounds__(64) k_gemm_short_x2(const NtArgs<float> p) {
+  constexpr int C = 1 + ND1;
+  constexpr int SU = C == 1 ? 8 : 5;
+  const int g = blockIdx.z;
+  const int lane = threadIdx.x;
+  const int hh = lane >> 5;
+  const int ntn = p.N / 32;
+  const int64_t lt = xcd_remap(blockIdx.x, gridDim.x);
+  const int64_t m0 = (lt / ntn) * 32;
+  const int n0 = (int)(lt % ntn) * 32;
+  const int64_t npts = p.seg.n_points;
+  const int nch = p.K / 16;
+  const bool pvalid = m0 + (lane & 31) < npts;
+  // points past the end read the last one (their results are never stored)
+  const int64_t pt = pvalid ? m0 + (lane & 31) : npts - 1;
+  // lane: row l & 31, eight k values 8 (l >> 5) of a chunk; the weight rows
+  // hold a chunk's 16 high pieces, then its 16 low pieces
+  const char* wp = (const char*)(p.Wm + g * p.w_g + (int64_t)(n0 + (lane & 31)) * p.ldw) + 16 * hh;
+  const char* xp[C];
+#pragma unroll
+  for (int k = 0; k < C; ++k)
+    xp[k] = (const char*)(p.X + g * p.x_g + (p.seg.row0 + k * p.seg.plane + pt) * p.ldx) + 32 * hh;
+  f32x16 acc[C];
+#pragma unroll
+  for (int k = 0; k < C; ++k)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[k][r] = 0.0f;
+  u32x4 wb[2][SU][2], xb[2][SU][C][2];
+  auto load = [&](int b, int c) {
+#pragma unroll
+    for (int i = 0; i < SU; ++i) {
+      const int64_t o = (int64_t)(c + i < nch ? c + i : nch - 1) * 64;   // (repeats of the last chunk are not multiplied)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        wb[b][i][h] = *(const u32x4*)(wp + o + 32 * h);
+#pragma unroll
+        for (int k = 0; k < C; ++k) xb[b][i][k][h] = *(const u32x4*)(xp[k] + o + 16 * h);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto mul = [&](int b, int c) {
+#pragma unroll
+    for (int i = 0; i < SU; ++i) {
+      if (c + i >= nch) break;
+      const bf16x8 bw[2] = {__builtin_bit_cast(bf16x8, wb[b][i][0]), __builtin_bit_cast(bf16x8, wb[b][i][1])};
+#pragma unroll
+      for (int k = 0; k < C; ++k) {
+        const u32x8 w = {xb[b][i][k][0].x, xb[b][i][k][0].y, xb[b][i][k][0].z, xb[b][i][k][0].w,
+                         xb[b][i][k][1].x, xb[b][i][k][1].y, xb[b][i][k][1].z, xb[b][i][k][1].w};
+        bf16x8 ax[2];
+        split_frag<2>(__builtin_bit_cast(f32x8, w), ax);
+        mma_split<2>(acc[k], bw, ax);
+      }
+    }
+  };
+  load(0, 0);
+  for (int c = 0; c < nch; c += 2 * SU) {
+    load(1, c + SU);
+    mul(0, c);
+    if (c + SU >= nch) break;
+    load(0, c + 2 * SU);
+    mul(1, c + SU);
+  }
+
+  // lane: point pt, columns n0 + 8 q + 4 hh + 0..3 in registers 4 q + 0..3
+  if constexpr (EPI == EPI_DF) {
+    const int64_t ldY = p.sY_ld > 0 ? p.sY_ld : p.nY, ldU = p.sU_ld > 0 ? p.sU_ld : p.nU;
+    if (!pvalid) return;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int n = n0 + 8 * (r >> 2) + 4 * hh + (r & 3);
+      const float v = p.df_sign * acc[0][r];
+      if (n < p.nY) p.seedY[g * p.sY_g + pt * ldY + n] = v;
+      else if (n < p.nY + p.nU) p.seedU[g * p.sU_g + pt * ldU + p.sU_off + (n - p.nY)] = v;
+    }
+  } else {
+    auto at = [&](auto* base, int k, int q) {
+      return base + g * p.o_g + (p.seg.row0 + k * p.seg.plane + pt) * p.ldo + n0 + 8 * q + 4 * hh;
+    };
+    auto put = [&](float* dst) {
+      if (!pvalid) return;
+#pragma unroll
+      for (int k = 0; k < C; ++k)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *(f32x4*)at(dst, k, q) = f32x4{acc[k][4 * q], acc[k][4 * q + 1], acc[k][4 * q + 2], acc[k][4 * q + 3]};
+    };
+    auto get = [&](f32x4 (&v)[C][4], const float* src) {
+#pragma unroll
+      for (int k = 0; k < C; ++k)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[k][q] = *(const f32x4*)at(src, k, q);
+    };
+    auto add = [&](const float* src) {
+      f32x4 v[C][4];
+      get(v, src);
+#pragma unroll
+      for (int k = 0; k < C; ++k)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[k][r] += v[k][r >> 2][r & 3];
+    };
+    if constexpr (EPI == EPI_FWD) {
+      const float* bp = p.bias + g * p.b_g + n0 + 4 * hh;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[0][r] += bp[8 * (r >> 2) + (r & 3)];
+      if (p.out_a) put(p.out_a);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        float v[C];
+#pragma unroll
+        for (int k = 0; k < C; ++k) v[k] = acc[k][r];
+        jet_fwd<ND1, 0>(v);
+#pragma unroll
+        for (int k = 0; k < C; ++k) acc[k][r] = v[k];
+      }
+      if (p.skip) add(p.skip);
+      put(p.out_h);
+    } else {
+      f32x4 ap[C][4];
+      get(ap, p.aprev);
+      if (p.skip_g) add(p.skip_g);
+      if (p.out_gh) put(p.out_gh);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        float gv[C], av[C];
+#pragma unroll
+        for (int k = 0; k < C; ++k) {
+          gv[k] = acc[k][r];
+          av[k] = ap[k][r >> 2][r & 3];
+        }
+        jet_bwd<ND1, 0>(gv, av);
+#pragma unroll
+        for (int k = 0; k < C; ++k) acc[k][r] = gv[k];
+      }
+      put(p.out_da);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // k_gemm_nt_wr: the products and epilogues of k_gemm_nt for 16-bit storage
 // and K = N = 128 (hidden layers of width 128), as a persistent kernel
 // built to keep HBM busy.  Each block copies the weight matrix into LDS once
@@ -2163,6 +2496,22 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
     if (a.pm != PM_NATIVE) {
       if (a.y || a.fp1) return hipErrorInvalidValue;
       if constexpr (C <= 2) {
+        // few output tiles.  us per forward launch, tiled -> short, rows x N x K
+        // (number of 32 x 32 blocks): split products 512 x 256 x 416 (128)
+        // 28.0 -> 10.1, 192 x 2048 x 8192 (384) 374 -> 122, 1024 x 1024 x 1024
+        // (1024) 58.6 -> 39.1, 4096 x 256 x 256 (1024) 22.0 -> 17.2 but 2048
+        // blocks 23.6 -> 29.3; K = 128: 512 blocks 12.1 -> 9.4, 1024 12.8 ->
+        // 13.9.  fp64 products 512 x 256 x 416 26.6 -> 10.6, 4096 x 128 x 128
+        // (512) 14.2 -> 10.5, 1024 blocks 15.2 -> 15.5
+        const int64_t sblocks = ((npts + 31) / 32) * (a.N / 32) * G;
+        const int64_t limit = (a.pm == PM_F64 ? 3 : a.K >= 256 ? 4 : 2) * (int64_t)cu_count();
+        if (a.pm != PM_SPLIT3 && a.N % 32 == 0 && a.K % 16 == 0 && sblocks <= limit) {
+          dim3 grid((unsigned)(((npts + 31) / 32) * (a.N / 32)), 1, G);
+          if (a.pm == PM_SPLIT2) k_gemm_short_x2<ND1, EPI><<<grid, 64, 0, st>>>(a);
+          else if (a.K >= 1024) k_gemm_short<ND1, EPI, 8><<<grid, 512, 0, st>>>(a);   // (eight waves share the contraction)
+          else k_gemm_short<ND1, EPI, 4><<<grid, 256, 0, st>>>(a);
+          return hipGetLastError();
+        }
         if (a.N <= 32 && a.pm != PM_F64) {
           dim3 grid((unsigned)(((npts + 127) / 128) * ((a.N + 31) / 32)), 1, G);
           if (a.pm == PM_SPLIT2) k_gemm_nt<T, ND1, ND2, 4, 1, 1, 1, EPI, 2, true, 0, PM_SPLIT2><<<grid, 256, 0, st>>>(a);

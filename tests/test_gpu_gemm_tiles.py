@@ -48,3 +48,28 @@ def test_gen_forward_tiles(d, order, W, dtype):
         check({f"c{k}": rel(got[k], ref[k]) for k in range(ref.shape[0])}, TOL[dtype], f"d={d} order={order} W={W}")
     assert torch.equal(small[0, :, 0], large[0, :, 0, :few])
     assert torch.equal(small[0, :, 0], large[0, :, 0, -few:])
+
+
+# fp32-stored products with few output tiles run as short launches (one wave per
+# tile in split products; in fp64 the contraction is shared among a
+# block's waves, four, eight from K = 1024), above that they are tiled: single
+# and ragged rows, contractions shorter than a block's waves and longer than
+# its prefetch, both sides of the dispatch (2000 x 1024 and 9000 x 128 are tiled
+# both ways)
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("G,B,n_in,L,W", [(1, 1, 3, 2, 32), (2, 33, 7, 3, 32), (1, 31, 1040, 2, 64), (1, 65, 40, 2, 1024),
+                                          (3, 17, 100, 2, 256), (1, 300, 2016, 2, 1024), (1, 9000, 128, 2, 128), (1, 2000, 64, 2, 1024)])
+def test_disc_forward_short(dtype, G, B, n_in, L, W):
+    import torch
+    print(f"disc_forward short G={G} B={B} n_in={n_in} L={L} W={W} {dtype}", flush=True)
+    rng = np.random.default_rng(B + n_in)
+    shape = (n_in, L, W)
+    p = np.stack([glorot_mlp(rng, *shape) for _ in range(G)])
+    p[:, -1] = 0.3
+    snap = rng.standard_normal((G, B, n_in)).astype(np.float32)
+    sc = pigan.disc_forward(to_dev(p), shape, to_dev(snap), dtype=dtype)
+    torch.cuda.synchronize()
+    sc = sc.cpu().numpy()
+    for g in range(G):
+        ref = oracle.mlp_forward(p[g], shape, snap[g])
+        check({f"g{g}": rel(sc[g], ref)}, TOL[dtype], f"disc_forward short {dtype}")
