@@ -295,8 +295,9 @@ static void plan_net(Carver& cv, NetBuf& nb, const pigan_mlp& m, int d, int nd2,
   const size_t nw = (size_t)std::max(L - 1, 1) * W * W * G;
   nb.wc = cv.take(nw * es * (es == 2 ? 2 : 1));
   nb.wcT = cv.take(nw * es);
-  nb.ws = cv.take(nw * 4);
-  nb.wsT = cv.take(nw * 4);
+  // fp32 storage: the same fp32 copies serve the sensor rows
+  nb.ws = es == 4 ? nb.wc : cv.take(nw * 4);
+  nb.wsT = es == 4 ? nb.wcT : cv.take(nw * 4);
   nb.nrc = first_bwd_chunks(Sc, (int64_t)P + n_s, W);
   nb.fb = cv.take((size_t)Sc * nb.nrc * 7 * W * 8 * G);
   nb.ppb_sen = ob_ppb(nb.n_sen, W);
@@ -521,14 +522,13 @@ static pigan_status weight_grad(const T* dA, int64_t a_g, int64_t lda, const T* 
   {
     ProfScope ps(st, "reduce_dw", 0.0, (pm_wide(pm) ? 8.0 : 4.0) * ((double)ns + 1.0) * N * Jp * G);
     const int64_t nw = (int64_t)N * Jp;
+    const ColSum<double> bias{pdb, (int64_t)ns * N, ns, N, 1, 1, gb, g_g};
     if (pm_wide(pm))
-      HIP_TRY(launch_colsum<double>((double*)part, (int64_t)ns * nw, ns, nw, nw, Jp, J, gW, g_g, accumulate, scale,
-                                    nonfinite, G, st));
+      HIP_TRY(launch_colsum<double>(ColSum<double>{(double*)part, (int64_t)ns * nw, ns, nw, Jp, J, gW, g_g}, &bias,
+                                    accumulate, scale, nonfinite, G, st));
     else
-      HIP_TRY(launch_colsum<float>((float*)part, (int64_t)ns * nw, ns, nw, nw, Jp, J, gW, g_g, accumulate, scale,
-                                   nonfinite, G, st));
-    HIP_TRY(launch_colsum<double>(pdb, (int64_t)ns * N, ns, N, N, 1, 1, gb, g_g, accumulate, scale, nonfinite, G,
-                                  st));
+      HIP_TRY(launch_colsum<float>(ColSum<float>{(float*)part, (int64_t)ns * nw, ns, nw, Jp, J, gW, g_g}, &bias,
+                                   accumulate, scale, nonfinite, G, st));
   }
   return PIGAN_OK;
 }
@@ -698,8 +698,9 @@ static pigan_status gen_chunk_bwd(void* ws, const StepPlan& pl, const NetBuf& nb
                  ((double)nb.n_sen * 4 + (double)mc * sizeof(T)) * W * (topskip ? 4 : 3) * G);
     HIP_TRY(launch_out2_bwd<float>(0, 0, os, G, st));
     HIP_TRY(launch_out2_bwd<T>(nb.nd1, nb.nd2, oc, G, st));
-    HIP_TRY(launch_colsum<double>(tp<double>(ws, nb.ob), (int64_t)n_slots * 2 * (W + 1), n_slots, 2 * (W + 1),
-                                  2 * (W + 1), 1, 1, grad + nb.off.wout, pg, accumulate, scale, nonfinite, G, st));
+    HIP_TRY(launch_colsum<double>(ColSum<double>{tp<double>(ws, nb.ob), (int64_t)n_slots * 2 * (W + 1), n_slots,
+                                                 2 * (W + 1), 1, 1, grad + nb.off.wout, pg},
+                                  nullptr, accumulate, scale, nonfinite, G, st));
   } else {
     OutBwdArgs<float> os{};
     os.A = tp<float>(ws, nb.As[L]); os.dA = tp<float>(ws, nb.dAs[0]); os.o_g = ags; os.ldo = W;
@@ -716,8 +717,9 @@ static pigan_status gen_chunk_bwd(void* ws, const StepPlan& pl, const NetBuf& nb
     ProfScope ps(st, "out_bwd", 0.0, ((double)nb.n_sen * 4 + (double)mc * sizeof(T)) * W * 2 * G);
     HIP_TRY(launch_out_bwd<float>(0, 0, os, G, st));
     HIP_TRY(launch_out_bwd<T>(nb.nd1, nb.nd2, oc, G, st));
-    HIP_TRY(launch_colsum<double>(tp<double>(ws, nb.ob), (int64_t)n_slots * (W + 1), n_slots, W + 1, W + 1, 1, 1,
-                                  grad + nb.off.wout, pg, accumulate, scale, nonfinite, G, st));
+    HIP_TRY(launch_colsum<double>(ColSum<double>{tp<double>(ws, nb.ob), (int64_t)n_slots * (W + 1), n_slots, W + 1, 1,
+                                                 1, grad + nb.off.wout, pg},
+                                  nullptr, accumulate, scale, nonfinite, G, st));
   }
   void* part = tp<void>(ws, pl.dwp);
   double* pdb = tp<double>(ws, pl.dwdb);
@@ -775,27 +777,32 @@ static pigan_status gen_chunk_bwd(void* ws, const StepPlan& pl, const NetBuf& nb
   return PIGAN_OK;
 }
 
+// A generator's weight copies: for the collocation rows forward weights (two
+// terms in 16-bit storage) and transposes in the storage type, for the sensor
+// rows fp32 copies and transposes (pre-split for the split products; in fp32
+// mode the collocation copies serve both).  fwd_only: what the sensor rows'
+// forward pass reads (a critic-only step of the paired or trunk generators).
 template <class T>
-static pigan_status cast_gen_weights(void* ws, const NetBuf& nb, const float* params, int G, hipStream_t st) {
+static CastSet<T> gen_casts(void* ws, const NetBuf& nb, const float* params, bool fwd_only) {
   const int W = nb.off.W, L = nb.off.L;
-  const int64_t dg = (int64_t)std::max(L - 1, 1) * W * W;
-  for (int l = 2; l <= L; ++l) {
-    const float* src = params + nb.off.w[l];
-    const size_t o = (size_t)(l - 2) * W * W;
-    if constexpr (two_term<T>()) {
-      HIP_TRY(launch_cast2<T>(src, nb.off.n, W, W, tp<T>(ws, nb.wc) + 2 * o, 2 * dg, G, st));
-      HIP_TRY(launch_cast<T>(src, nb.off.n, W, W, W, nullptr, tp<T>(ws, nb.wcT) + o, dg, G, st));
-    } else {
-      HIP_TRY(launch_cast<T>(src, nb.off.n, W, W, W, tp<T>(ws, nb.wc) + o, tp<T>(ws, nb.wcT) + o, dg, G, st));
-    }
-    // the sensor rows' copies: pre-split for the split products
-    if constexpr (adv_pm<T>() == PM_SPLIT2)
-      HIP_TRY(launch_cast_pair(src, nb.off.n, W, W, W, tp<float>(ws, nb.ws) + o, tp<float>(ws, nb.wsT) + o, dg, G,
-                               st));
-    else
-      HIP_TRY(launch_cast<float>(src, nb.off.n, W, W, W, tp<float>(ws, nb.ws) + o, tp<float>(ws, nb.wsT) + o, dg, G,
-                                 st));
-  }
+  constexpr bool pair = adv_pm<T>() == PM_SPLIT2;
+  CastSet<T> c{};
+  if (L < 2) return c;
+  c.src = params + nb.off.w[2]; c.s_g = nb.off.n; c.s_l = (int64_t)W * W + W; c.layers = L - 1;
+  c.N = c.K = c.Kp = W; c.d_g = (int64_t)(L - 1) * W * W;
+  if constexpr (two_term<T>()) c.two = fwd_only ? nullptr : tp<T>(ws, nb.wc);
+  if (two_term<T>() && !fwd_only) c.tT = tp<T>(ws, nb.wcT);
+  c.f = tp<float>(ws, nb.ws);
+  c.fT = fwd_only ? nullptr : tp<float>(ws, nb.wsT);
+  c.pair = pair;
+  return c;
+}
+
+template <class T>
+static pigan_status cast_gen_weights(void* ws, const StepPlan& pl, const float* pY, const float* pU, int G,
+                                     hipStream_t st, bool fwd_only = false) {
+  HIP_TRY(launch_cast_layers<T>(gen_casts<T>(ws, pl.Y, pY, fwd_only),
+                                pl.trunk ? CastSet<T>{} : gen_casts<T>(ws, pl.U, pU, fwd_only), G, st));
   return PIGAN_OK;
 }
 
@@ -804,15 +811,16 @@ static pigan_status cast_gen_weights(void* ws, const NetBuf& nb, const float* pa
 // pair: pre-split for the split products)
 static pigan_status cast_disc_weights(void* ws, const DiscBuf& D, const float* pD, int WD, int LD, int n_in, int G,
                                       hipStream_t st, bool pair) {
-  auto cast = [&](const float* src, int N, int K, int Kp, float* dst, float* dstT, int64_t d_g) {
-    return pair ? launch_cast_pair(src, D.off.n, N, K, Kp, dst, dstT, d_g, G, st)
-                : launch_cast<float>(src, D.off.n, N, K, Kp, dst, dstT, d_g, G, st);
-  };
-  HIP_TRY(cast(pD + D.off.w[1], WD, n_in, D.Kp, tp<float>(ws, D.w1), tp<float>(ws, D.w1T), (int64_t)WD * D.Kp));
-  const int64_t dgl = (int64_t)std::max(LD - 1, 1) * WD * WD;
-  for (int l = 2; l <= LD; ++l)
-    HIP_TRY(cast(pD + D.off.w[l], WD, WD, WD, tp<float>(ws, D.wc) + (size_t)(l - 2) * WD * WD,
-                 tp<float>(ws, D.wcT) + (size_t)(l - 2) * WD * WD, dgl));
+  CastSet<float> c0{}, c1{};
+  c0.src = pD + D.off.w[1]; c0.s_g = D.off.n; c0.layers = 1;
+  c0.N = WD; c0.K = n_in; c0.Kp = D.Kp; c0.d_g = (int64_t)WD * D.Kp;
+  c0.f = tp<float>(ws, D.w1); c0.fT = tp<float>(ws, D.w1T); c0.pair = pair;
+  if (LD > 1) {
+    c1.src = pD + D.off.w[2]; c1.s_g = D.off.n; c1.s_l = (int64_t)WD * WD + WD; c1.layers = LD - 1;
+    c1.N = c1.K = c1.Kp = WD; c1.d_g = (int64_t)(LD - 1) * WD * WD;
+    c1.f = tp<float>(ws, D.wc); c1.fT = tp<float>(ws, D.wcT); c1.pair = pair;
+  }
+  HIP_TRY(launch_cast_layers<float>(c0, c1, G, st));
   return PIGAN_OK;
 }
 
@@ -913,8 +921,9 @@ static pigan_status critic_penalty(void* ws, const StepPlan& pl, const pigan_ste
   {
     ProfScope ps(st, "gp_bwd", 0.0, (double)2 * n * WD * 2 * 4 * G);
     HIP_TRY(launch_out_bwd<float>(1, 0, ob, G, st));
-    HIP_TRY(launch_colsum<double>(tp<double>(ws, D.ob), (int64_t)ob.n_slots * (WD + 1), ob.n_slots, WD + 1, WD + 1,
-                                  1, 1, gD + D.off.wout, D.off.n, 1, inv, nonfinite, G, st));
+    HIP_TRY(launch_colsum<double>(ColSum<double>{tp<double>(ws, D.ob), (int64_t)ob.n_slots * (WD + 1), ob.n_slots,
+                                                 WD + 1, 1, 1, gD + D.off.wout, D.off.n},
+                                  nullptr, 1, inv, nonfinite, G, st));
   }
   cur = 0;
   for (int l = LD; l >= 2; --l) {
@@ -967,8 +976,9 @@ static pigan_status disc_pass(void* ws, const StepPlan& pl, const float* pD, int
     ob.slot0 = 0; ob.seg = Seg{B, 0, 0}; ob.exact = pm == PM_F64;
     ProfScope ps(st, "out_bwd", 0.0, (double)B * WD * 2 * 4 * G);
     HIP_TRY(launch_out_bwd<float>(0, 0, ob, G, st));
-    HIP_TRY(launch_colsum<double>(tp<double>(ws, D.ob), (int64_t)ob.n_slots * (WD + 1), ob.n_slots, WD + 1, WD + 1,
-                                  1, 1, gD + D.off.wout, D.off.n, accum, inv, nonfinite, G, st));
+    HIP_TRY(launch_colsum<double>(ColSum<double>{tp<double>(ws, D.ob), (int64_t)ob.n_slots * (WD + 1), ob.n_slots,
+                                                 WD + 1, 1, 1, gD + D.off.wout, D.off.n},
+                                  nullptr, accum, inv, nonfinite, G, st));
   }
   int cur = 0;
   for (int l = LD; l >= 2; --l) {
@@ -1021,8 +1031,7 @@ static pigan_status run_step(const pigan_step_desc* s, const StepPlan& pl, const
   {
     ProfScope ps(st, "misc", 0.0, 0.0);
     HIP_TRY(launch_zero(acc, 4 * G, nonfinite, st));
-    if ((r = cast_gen_weights<T>(ws, pl.Y, pY, G, st)) != PIGAN_OK) return r;
-    if (!pl.trunk && (r = cast_gen_weights<T>(ws, pl.U, pU, G, st)) != PIGAN_OK) return r;
+    if ((r = cast_gen_weights<T>(ws, pl, pY, pU, G, st, s->critic_only)) != PIGAN_OK) return r;
     if (pl.trunk)   // the trunk sees both sensor sets: locations [Y sensors ; u sensors]
       HIP_TRY(launch_concat_rows(xsY, (int64_t)s->n_sY * d, s->n_sY, xsU, (int64_t)s->n_sU * d, s->n_sU, d,
                                  tp<float>(ws, pl.Y.xsc), (int64_t)(s->n_sY + s->n_sU) * d, G, st));
@@ -1161,8 +1170,7 @@ static pigan_status run_hier(const pigan_step_desc* s, const StepPlan& pl, const
   {
     ProfScope ps(st, "misc", 0.0, 0.0);
     HIP_TRY(launch_zero(acc, 4 * GD, nonfinite, st));
-    if ((r = cast_gen_weights<T>(ws, pl.Y, pY, 1, st)) != PIGAN_OK) return r;
-    if (!pl.trunk && (r = cast_gen_weights<T>(ws, pl.U, pU, 1, st)) != PIGAN_OK) return r;
+    if ((r = cast_gen_weights<T>(ws, pl, pY, pU, 1, st)) != PIGAN_OK) return r;
     if (pl.trunk)   // the trunk sees both sensor sets: locations [Y sensors ; u sensors]
       HIP_TRY(launch_concat_rows(xsY, (int64_t)s->n_sY * d, s->n_sY, xsU, (int64_t)s->n_sU * d, s->n_sU, d,
                                  tp<float>(ws, pl.Y.xsc), (int64_t)(s->n_sY + s->n_sU) * d, 1, st));
@@ -1728,10 +1736,12 @@ static pigan_status run_gen_fwd(const pigan_mlp* net, const float* params, int d
   const int64_t dg = (int64_t)std::max(L - 1, 1) * W * W * tw;
   {
     ProfScope ps(st, "misc", 0.0, 0.0);
-    for (int l = 2; l <= L; ++l) {
-      T* dst = tp<T>(ws, p.wc) + (size_t)(l - 2) * W * W * tw;
-      if constexpr (two_term<T>()) HIP_TRY(launch_cast2<T>(params + off.w[l], off.n, W, W, dst, dg, G, st));
-      else HIP_TRY(launch_cast<T>(params + off.w[l], off.n, W, W, W, dst, nullptr, dg, G, st));
+    if (L > 1) {
+      CastSet<T> c{};
+      c.src = params + off.w[2]; c.s_g = off.n; c.s_l = (int64_t)W * W + W; c.layers = L - 1;
+      c.N = c.K = c.Kp = W; c.d_g = (int64_t)(L - 1) * W * W;
+      (two_term<T>() ? c.two : c.t) = tp<T>(ws, p.wc);
+      HIP_TRY(launch_cast_layers<T>(c, CastSet<T>{}, G, st));
     }
     HIP_TRY(launch_zproj(params, off.n, in_dim, d, W, z, (int64_t)S * n_z, n_z, S, tp<float>(ws, p.zp),
                          (int64_t)S * W, G, st));
@@ -1869,14 +1879,15 @@ static pigan_status run_disc_fwd(const pigan_mlp* net, const float* params, cons
   {
     ProfScope ps(st, "misc", 0.0, 0.0);
     // weight copies (pre-split for the split products)
-    auto cast = [&](const float* src, int N, int K, int Kp, float* dst, int64_t d_g) {
-      return adv_pm<T>() == PM_SPLIT2 ? launch_cast_pair(src, off.n, N, K, Kp, dst, nullptr, d_g, G, st)
-                                      : launch_cast<float>(src, off.n, N, K, Kp, dst, nullptr, d_g, G, st);
-    };
-    HIP_TRY(cast(params + off.w[1], W, n_in, p.Kp, tp<float>(ws, p.w1), (int64_t)W * p.Kp));
-    const int64_t dg = (int64_t)std::max(L - 1, 1) * W * W;
-    for (int l = 2; l <= L; ++l)
-      HIP_TRY(cast(params + off.w[l], W, W, W, tp<float>(ws, p.wc) + (size_t)(l - 2) * W * W, dg));
+    constexpr bool pair = adv_pm<T>() == PM_SPLIT2;
+    CastSet<float> c0{}, c1{};
+    c0.src = params + off.w[1]; c0.s_g = off.n; c0.layers = 1;
+    c0.N = W; c0.K = n_in; c0.Kp = p.Kp; c0.d_g = (int64_t)W * p.Kp; c0.f = tp<float>(ws, p.w1); c0.pair = pair;
+    if (L > 1) {
+      c1.src = params + off.w[2]; c1.s_g = off.n; c1.s_l = (int64_t)W * W + W; c1.layers = L - 1;
+      c1.N = c1.K = c1.Kp = W; c1.d_g = (int64_t)(L - 1) * W * W; c1.f = tp<float>(ws, p.wc); c1.pair = pair;
+    }
+    HIP_TRY(launch_cast_layers<float>(c0, c1, G, st));
     HIP_TRY(launch_snap_fill<float>(nullptr, 0, nullptr, 0, 0, 0, 0, snap, (int64_t)B * n_in, B, n_in,
                                     tp<float>(ws, p.X0), (int64_t)B * p.Kp, p.Kp, G, st));
   }

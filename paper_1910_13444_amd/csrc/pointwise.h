@@ -117,10 +117,14 @@ hipError_t launch_hier_scatter(const HierSnap& h, const float* dX, int64_t dx_g,
 hipError_t launch_hier_pde_loss(const double* acc, int slot, float lambda_pde, int64_t SP, float* loss, int D,
                                 int32_t* nonfinite, hipStream_t st);
 // dst[(col/Jp)*J + col%Jp] (+)= scale * sum_slots part[g][slot][col]  (fp64, fixed order)
+template <class Tin> struct ColSum {
+  const Tin* part; int64_t p_g; int n_slots; int64_t ncols;   // [G][n_slots][ncols], groups p_g apart
+  int Jp; int J; float* dst; int64_t d_g;
+};
+// w, and in the same launch a layer's bias sums (or null)
 template <class Tin>
-hipError_t launch_colsum(const Tin* part, int64_t p_g, int n_slots, int64_t slot_stride, int64_t ncols, int Jp, int J,
-                         float* dst, int64_t d_g, int accumulate, float scale, int32_t* nonfinite, int G,
-                         hipStream_t st);
+hipError_t launch_colsum(const ColSum<Tin>& w, const ColSum<double>* bias, int accumulate, float scale,
+                         int32_t* nonfinite, int G, hipStream_t st);
 template <class T> hipError_t launch_first_bwd(const FirstBwdArgs<T>& a, int G, hipStream_t st);
 hipError_t launch_first_wgrad(const double* part, int S, int nrc, int W, int d, int nd1, int in_dim, const float* z,
                               int64_t z_g, int n_z, float* grad, int64_t g_g, int accumulate, float scale,
@@ -129,14 +133,17 @@ hipError_t launch_losses(const double* acc, int acc_stride, const float* w_group
                          float lambda_pde, float lambda_gp, int n_gp, float* loss, float* gp, int32_t* nonfinite,
                          int G, hipStream_t st);
 hipError_t launch_zero(double* acc, int n, int32_t* flag, hipStream_t st);
+// copies of `layers` weight matrices [N][K] (s_l floats apart in the packed
+// parameters, outputs N * Kp elements apart; null outputs are not written)
+template <class T> struct CastSet {
+  const float* src; int64_t s_g; int64_t s_l; int layers; int N; int K; int Kp;
+  T* two;                    // rows [hi | lo], 2 Kp wide (groups 2 d_g apart)
+  T* t; T* tT;               // rounded to T; transposed
+  float* f; float* fT;       // fp32; transposed (pair: split bf16 pieces)
+  int pair; int64_t d_g;
+};
+// two sets in one launch (the second may be empty: layers = 0)
 template <class T>
-hipError_t launch_cast(const float* src, int64_t s_g, int N, int K, int Kp, T* dst, T* dstT, int64_t d_g, int G,
-                       hipStream_t st);
-// split-product weight copies (pair-blocked bf16 pieces in fp32-pitch rows)
-hipError_t launch_cast_pair(const float* src, int64_t s_g, int N, int K, int Kp, float* dst, float* dstT, int64_t d_g,
-                            int G, hipStream_t st);
-// two-term weights [hi | lo] per row (16-bit storage), rows 2 K wide
-template <class T>
-hipError_t launch_cast2(const float* src, int64_t s_g, int N, int K, T* dst, int64_t d_g, int G, hipStream_t st);
+hipError_t launch_cast_layers(const CastSet<T>& c0, const CastSet<T>& c1, int G, hipStream_t st);
 
 }  // namespace pigan

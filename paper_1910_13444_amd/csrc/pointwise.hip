@@ -760,23 +760,21 @@ __global__ void k_hier_pde_loss(const double* __restrict__ acc, int slot, float 
 // Few columns take many slot groups so that a launch still spans the chip.
 // ---------------------------------------------------------------------------
 template <class Tin, int VEC, int SG>
-__global__ void __launch_bounds__(256)
-k_colsum(const Tin* __restrict__ part, int64_t p_g, int n_slots, int64_t slot_stride, int64_t ncols, int Jp, int J,
-         float* dst, int64_t d_g, int accumulate, float scale, int32_t* nonfinite) {
+__device__ __forceinline__ void colsum_block(const ColSum<Tin>& c, int64_t blk, int g, float scale, int accumulate,
+                                             int32_t* nonfinite, double* red) {
   constexpr int LANES = 256 / SG;
-  __shared__ double red[SG][LANES * VEC];
-  const int g = blockIdx.z;
+  constexpr int ROW = LANES * VEC;                 // red: [SG][ROW]
   const int lane = threadIdx.x % LANES, grp = threadIdx.x / LANES;
-  const int64_t col0 = ((int64_t)blockIdx.x * LANES + lane) * VEC;
+  const int64_t col0 = (blk * LANES + lane) * VEC;
   double s[VEC];
 #pragma unroll
   for (int e = 0; e < VEC; ++e) s[e] = 0.0;
-  if (col0 < ncols) {
-    const Tin* src = part + g * p_g + col0;
+  if (col0 < c.ncols) {
+    const Tin* src = c.part + g * c.p_g + col0;
     if constexpr (VEC == 4) {
 #pragma unroll 4
-      for (int q = grp; q < n_slots; q += SG) {
-        const float4 v = *(const float4*)(src + (int64_t)q * slot_stride);
+      for (int q = grp; q < c.n_slots; q += SG) {
+        const float4 v = *(const float4*)(src + (int64_t)q * c.ncols);
         s[0] += (double)v.x;
         s[1] += (double)v.y;
         s[2] += (double)v.z;
@@ -784,29 +782,29 @@ k_colsum(const Tin* __restrict__ part, int64_t p_g, int n_slots, int64_t slot_st
       }
     } else {
 #pragma unroll 8
-      for (int q = grp; q < n_slots; q += SG) s[0] += (double)src[(int64_t)q * slot_stride];
+      for (int q = grp; q < c.n_slots; q += SG) s[0] += (double)src[(int64_t)q * c.ncols];
     }
   }
 #pragma unroll
-  for (int e = 0; e < VEC; ++e) red[grp][lane * VEC + e] = s[e];
+  for (int e = 0; e < VEC; ++e) red[grp * ROW + lane * VEC + e] = s[e];
   __syncthreads();
 #pragma unroll
   for (int h = SG / 2; h >= 1; h >>= 1) {
     if (grp < h) {
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) red[grp][lane * VEC + e] += red[grp + h][lane * VEC + e];
+      for (int e = 0; e < VEC; ++e) red[grp * ROW + lane * VEC + e] += red[(grp + h) * ROW + lane * VEC + e];
     }
     __syncthreads();
   }
-  if (grp == 0 && col0 < ncols) {
+  if (grp == 0 && col0 < c.ncols) {
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
       const int64_t col = col0 + e;
-      const double v = red[0][lane * VEC + e];
-      const int64_t n = col / Jp;
-      const int j = (int)(col % Jp);
-      if (j < J) {
-        float* o = dst + g * d_g + n * J + j;
+      const double v = red[lane * VEC + e];
+      const int64_t n = col / c.Jp;
+      const int j = (int)(col % c.Jp);
+      if (j < c.J) {
+        float* o = c.dst + g * c.d_g + n * c.J + j;
         float r = (float)(v * (double)scale);
         if (accumulate) r += *o;
         *o = r;
@@ -814,6 +812,22 @@ k_colsum(const Tin* __restrict__ part, int64_t p_g, int n_slots, int64_t slot_st
       }
     }
   }
+}
+
+// weights in blocks [0, blocks_w), biases (fp64 partials, one column per lane,
+// sgb slot groups) in the rest: one launch for a layer's two sums
+template <class Tin, int VEC, int SG>
+__global__ void __launch_bounds__(256)
+k_colsum(const ColSum<Tin> w, int blocks_w, const ColSum<double> b, int sgb, float scale, int accumulate,
+         int32_t* nonfinite) {
+  __shared__ double red[256 * VEC];
+  const int g = blockIdx.z;
+  const int blk = (int)blockIdx.x - blocks_w;
+  if (blk < 0) colsum_block<Tin, VEC, SG>(w, blockIdx.x, g, scale, accumulate, nonfinite, red);
+  else if (sgb == 1) colsum_block<double, 1, 1>(b, blk, g, scale, accumulate, nonfinite, red);
+  else if (sgb == 8) colsum_block<double, 1, 8>(b, blk, g, scale, accumulate, nonfinite, red);
+  else if (sgb == 32) colsum_block<double, 1, 32>(b, blk, g, scale, accumulate, nonfinite, red);
+  else colsum_block<double, 1, 128>(b, blk, g, scale, accumulate, nonfinite, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -999,42 +1013,20 @@ __global__ void k_zero(double* acc, int n, int32_t* flag) {
 }
 
 // ---------------------------------------------------------------------------
-// weight casts: src fp32 [N][K] -> dst [N][Kp] (zero padded) and optionally
-// dstT [Kp][N].  With dstT, k_cast_tr goes through 32 x 32 tiles in LDS so
-// that both outputs are stored in whole rows (a direct transposed store
-// writes one element per row of dstT); k_cast serves dst alone.
+// weight copies: every form that a step's GEMMs read of up to two sets of
+// layers, in one launch (a launch per layer and form took 4 us each: 18 of
+// them at 4 x 128, 65 us of an 821 us critic update).  A block owns one 32 x
+// 32 tile of one layer [N][K] (fp32, columns K..Kp read as zero):
+//   two : rows [hi | lo] of the storage type, 2 Kp wide: hi = W rounded to the
+//         storage type, lo = W - hi rounded likewise (two-term weights)
+//   t, tT : W rounded to T, rows Kp wide / transposed, rows N wide
+//   f, fT : fp32 copies, rows Kp wide / transposed; pair: every 16-element
+//         block of a row as its 16 high bf16 pieces followed by its 16 low
+//         pieces (hi = RNE(w), lo = RNE(w - hi)): the rows keep the fp32 byte
+//         pitch, and a 64-byte k-slice of a row is exactly the split layout
+//         the split-product GEMM stages in LDS
+// Transposes go through LDS so that every output is stored in whole rows.
 // ---------------------------------------------------------------------------
-template <class T>
-__global__ void __launch_bounds__(256)
-k_cast_tr(const float* __restrict__ src, int64_t s_g, int N, int K, int Kp, T* __restrict__ dst,
-          T* __restrict__ dstT, int64_t d_g) {
-  __shared__ T tile[32][33];
-  const int g = blockIdx.z;
-  const int k0 = blockIdx.x * 32, n0 = blockIdx.y * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-#pragma unroll
-  for (int r = ty; r < 32; r += 8) {
-    const int n = n0 + r, k = k0 + tx;
-    T tv = Elem<T>::from_f(0.0f);
-    if (n < N && k < Kp) {
-      tv = Elem<T>::from_f(k < K ? src[g * s_g + (int64_t)n * K + k] : 0.0f);
-      if (dst) dst[g * d_g + (int64_t)n * Kp + k] = tv;
-    }
-    tile[r][tx] = tv;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int r = ty; r < 32; r += 8) {
-    const int k = k0 + r, n = n0 + tx;
-    if (k < Kp && n < N) dstT[g * d_g + (int64_t)k * N + n] = tile[tx][r];
-  }
-}
-
-// split-product weight copies: fp32 src [N][K] -> dst [N][Kp] and dstT
-// [Kp][N] with every 16-element block of a row stored as its 16 high bf16
-// pieces followed by its 16 low pieces (hi = RNE(w), lo = RNE(w - hi)): the
-// rows keep the fp32 byte pitch, and a 64-byte k-slice of a row is exactly
-// the split layout the split-product GEMM stages in LDS (padding: zeros)
 __device__ __forceinline__ void pair_put(bf16* row, int k, float v) {
   const bf16 hi = (bf16)v;
   const bf16 lo = (bf16)(v - (float)hi);
@@ -1042,60 +1034,55 @@ __device__ __forceinline__ void pair_put(bf16* row, int k, float v) {
   row[32 * (k >> 4) + 16 + (k & 15)] = lo;
 }
 
-__global__ void __launch_bounds__(256)
-k_cast_pair(const float* __restrict__ src, int64_t s_g, int N, int K, int Kp, float* __restrict__ dst,
-            float* __restrict__ dstT, int64_t d_g) {
+template <class T>
+__global__ void __launch_bounds__(256) k_cast_layers(const CastSet<T> c0, const CastSet<T> c1, int blocks0) {
   __shared__ float tile[32][33];
+  const bool first = (int)blockIdx.x < blocks0;
+  const CastSet<T>& c = first ? c0 : c1;
   const int g = blockIdx.z;
-  const int k0 = blockIdx.x * 32, n0 = blockIdx.y * 32;
+  const int tk = (c.Kp + 31) / 32, tn = (c.N + 31) / 32;
+  int b = (int)blockIdx.x - (first ? 0 : blocks0);
+  const int l = b / (tk * tn);
+  b -= l * tk * tn;
+  const int k0 = (b % tk) * 32, n0 = (b / tk) * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  bf16* d = dst ? (bf16*)(dst + g * d_g) : nullptr;
-  bf16* dT = dstT ? (bf16*)(dstT + g * d_g) : nullptr;
+  const int N = c.N, K = c.K, Kp = c.Kp;
+  const float* src = c.src + g * c.s_g + l * c.s_l;
+  const int64_t o = g * c.d_g + (int64_t)l * N * Kp;
 #pragma unroll
   for (int r = ty; r < 32; r += 8) {
     const int n = n0 + r, k = k0 + tx;
     float v = 0.0f;
     if (n < N && k < Kp) {
-      v = k < K ? src[g * s_g + (int64_t)n * K + k] : 0.0f;
-      if (dst) pair_put(d + (int64_t)n * 2 * Kp, k, v);
+      v = k < K ? src[(int64_t)n * K + k] : 0.0f;
+      const int64_t e = o + (int64_t)n * Kp + k;
+      if (c.two) {
+        const T hi = Elem<T>::from_f(v);
+        c.two[2 * o + (int64_t)n * 2 * Kp + k] = hi;
+        c.two[2 * o + (int64_t)n * 2 * Kp + Kp + k] = Elem<T>::from_f(v - Elem<T>::to_f(hi));
+      }
+      if (c.t) c.t[e] = Elem<T>::from_f(v);
+      if (c.f) {
+        if (c.pair) pair_put((bf16*)(c.f + o) + (int64_t)n * 2 * Kp, k, v);
+        else c.f[e] = v;
+      }
     }
     tile[r][tx] = v;
   }
-  if (!dstT) return;
+  if (!c.tT && !c.fT) return;
   __syncthreads();
 #pragma unroll
   for (int r = ty; r < 32; r += 8) {
     const int k = k0 + r, n = n0 + tx;
-    if (k < Kp && n < N) pair_put(dT + (int64_t)k * 2 * N, n, tile[tx][r]);
+    if (k >= Kp || n >= N) continue;
+    const float v = tile[tx][r];
+    const int64_t e = o + (int64_t)k * N + n;
+    if (c.tT) c.tT[e] = Elem<T>::from_f(v);
+    if (c.fT) {
+      if (c.pair) pair_put((bf16*)(c.fT + o) + (int64_t)k * 2 * N, n, v);
+      else c.fT[e] = v;
+    }
   }
-}
-
-// two-term weights: dst[n] = [hi(W[n][:]) | lo(W[n][:])] (2 K wide), with
-// hi = W rounded to the storage type and lo = W - hi rounded likewise
-template <class T>
-__global__ void k_cast2(const float* __restrict__ src, int64_t s_g, int N, int K, T* __restrict__ dst, int64_t d_g) {
-  const int g = blockIdx.z;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)N * K) return;
-  const int64_t n = idx / K, k = idx % K;
-  const float v = src[g * s_g + idx];
-  const T hi = Elem<T>::from_f(v);
-  const T lo = Elem<T>::from_f(v - Elem<T>::to_f(hi));
-  dst[g * d_g + n * 2 * K + k] = hi;
-  dst[g * d_g + n * 2 * K + K + k] = lo;
-}
-
-template <class T>
-__global__ void k_cast(const float* __restrict__ src, int64_t s_g, int N, int K, int Kp, T* __restrict__ dst,
-                       T* __restrict__ dstT, int64_t d_g) {
-  const int g = blockIdx.z;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)N * Kp) return;
-  const int n = (int)(idx / Kp), k = (int)(idx % Kp);
-  const float v = k < K ? src[g * s_g + (int64_t)n * K + k] : 0.0f;
-  const T tv = Elem<T>::from_f(v);
-  if (dst) dst[g * d_g + idx] = tv;
-  if (dstT) dstT[g * d_g + (int64_t)k * N + n] = tv;
 }
 
 // ===========================================================================
@@ -1299,26 +1286,32 @@ hipError_t launch_fill_f32(float* p, int64_t n, int64_t p_g, float v, int G, hip
   return hipGetLastError();
 }
 
+// the fewest slot groups that still give 256 blocks (and no more groups than
+// slots; one group when there are at most two slots)
+static int colsum_groups(int64_t lanes, int n_slots, int G) {
+  int sg = n_slots <= 2 ? 1 : 8;
+  while (sg >= 8 && sg < 128 && 2 * sg <= n_slots && (lanes + 256 / sg - 1) / (256 / sg) * G < 256) sg *= 4;
+  return sg;
+}
+
 template <class Tin>
-hipError_t launch_colsum(const Tin* part, int64_t p_g, int n_slots, int64_t slot_stride, int64_t ncols, int Jp, int J,
-                         float* dst, int64_t d_g, int accumulate, float scale, int32_t* nonfinite, int G,
-                         hipStream_t st) {
-  if (ncols <= 0) return hipSuccess;
+hipError_t launch_colsum(const ColSum<Tin>& w, const ColSum<double>* bias, int accumulate, float scale,
+                         int32_t* nonfinite, int G, hipStream_t st) {
+  if (w.ncols <= 0) return hipSuccess;
   // four columns per lane where every slot row and group slab is 16-byte
   // aligned and whole (the workspace is 256-byte aligned)
   int vec = 1;
   if constexpr (sizeof(Tin) == 4) {
-    if (ncols % 4 == 0 && slot_stride % 4 == 0 && p_g % 4 == 0 && ((uintptr_t)part & 15) == 0) vec = 4;
+    if (w.ncols % 4 == 0 && w.p_g % 4 == 0 && ((uintptr_t)w.part & 15) == 0) vec = 4;
   }
-  // the fewest slot groups that still give 256 blocks (and no more groups than
-  // slots; one group when there are at most two slots)
-  const int64_t lanes = (ncols + vec - 1) / vec;
-  int sg = n_slots <= 2 ? 1 : 8;
-  while (sg >= 8 && sg < 128 && 2 * sg <= n_slots && (lanes + 256 / sg - 1) / (256 / sg) * G < 256) sg *= 4;
+  const int64_t lanes = (w.ncols + vec - 1) / vec;
+  const int sg = colsum_groups(lanes, w.n_slots, G);
   const unsigned nb = (unsigned)((lanes + 256 / sg - 1) / (256 / sg));
-#define PIGAN_COLSUM(V, S)                                                                                      \
-  k_colsum<Tin, V, S><<<dim3(nb, 1, G), 256, 0, st>>>(part, p_g, n_slots, slot_stride, ncols, Jp, J, dst, d_g, \
-                                                      accumulate, scale, nonfinite)
+  const ColSum<double> b = bias ? *bias : ColSum<double>{};
+  const int sgb = bias ? colsum_groups(b.ncols, b.n_slots, G) : 1;
+  const unsigned nbb = bias ? (unsigned)((b.ncols + 256 / sgb - 1) / (256 / sgb)) : 0;
+#define PIGAN_COLSUM(V, S) \
+  k_colsum<Tin, V, S><<<dim3(nb + nbb, 1, G), 256, 0, st>>>(w, (int)nb, b, sgb, scale, accumulate, nonfinite)
   if constexpr (sizeof(Tin) == 4) {
     if (vec == 4) {
       if (sg == 1) PIGAN_COLSUM(4, 1);
@@ -1335,10 +1328,10 @@ hipError_t launch_colsum(const Tin* part, int64_t p_g, int n_slots, int64_t slot
 #undef PIGAN_COLSUM
   return hipGetLastError();
 }
-template hipError_t launch_colsum<float>(const float*, int64_t, int, int64_t, int64_t, int, int, float*, int64_t, int,
-                                         float, int32_t*, int, hipStream_t);
-template hipError_t launch_colsum<double>(const double*, int64_t, int, int64_t, int64_t, int, int, float*, int64_t,
-                                          int, float, int32_t*, int, hipStream_t);
+template hipError_t launch_colsum<float>(const ColSum<float>&, const ColSum<double>*, int, float, int32_t*, int,
+                                         hipStream_t);
+template hipError_t launch_colsum<double>(const ColSum<double>&, const ColSum<double>*, int, float, int32_t*, int,
+                                          hipStream_t);
 
 template <class T>
 hipError_t launch_first_bwd(const FirstBwdArgs<T>& a, int G, hipStream_t st) {
@@ -1373,31 +1366,14 @@ hipError_t launch_zero(double* acc, int n, int32_t* flag, hipStream_t st) {
 }
 
 template <class T>
-hipError_t launch_cast(const float* src, int64_t s_g, int N, int K, int Kp, T* dst, T* dstT, int64_t d_g, int G,
-                       hipStream_t st) {
-  if (dstT)
-    k_cast_tr<T><<<dim3((unsigned)((Kp + 31) / 32), (unsigned)((N + 31) / 32), G), 256, 0, st>>>(src, s_g, N, K, Kp,
-                                                                                                dst, dstT, d_g);
-  else
-    k_cast<T><<<dim3(nblk((int64_t)N * Kp, 256), 1, G), 256, 0, st>>>(src, s_g, N, K, Kp, dst, dstT, d_g);
+hipError_t launch_cast_layers(const CastSet<T>& c0, const CastSet<T>& c1, int G, hipStream_t st) {
+  auto blocks = [](const CastSet<T>& c) { return (int64_t)c.layers * ((c.Kp + 31) / 32) * ((c.N + 31) / 32); };
+  const int64_t b0 = blocks(c0), b1 = blocks(c1);
+  if (b0 + b1 <= 0) return hipSuccess;
+  if (b0 + b1 > 0x7fffffff) return hipErrorInvalidValue;
+  k_cast_layers<T><<<dim3((unsigned)(b0 + b1), 1, G), 256, 0, st>>>(c0, c1, (int)b0);
   return hipGetLastError();
 }
-
-hipError_t launch_cast_pair(const float* src, int64_t s_g, int N, int K, int Kp, float* dst, float* dstT, int64_t d_g,
-                            int G, hipStream_t st) {
-  if (Kp % 16 != 0 || (dstT && N % 16 != 0)) return hipErrorInvalidValue;   // whole 16-element blocks per row
-  k_cast_pair<<<dim3((unsigned)((Kp + 31) / 32), (unsigned)((N + 31) / 32), G), 256, 0, st>>>(src, s_g, N, K, Kp, dst,
-                                                                                            dstT, d_g);
-  return hipGetLastError();
-}
-
-template <class T>
-hipError_t launch_cast2(const float* src, int64_t s_g, int N, int K, T* dst, int64_t d_g, int G, hipStream_t st) {
-  k_cast2<T><<<dim3(nblk((int64_t)N * K, 256), 1, G), 256, 0, st>>>(src, s_g, N, K, dst, d_g);
-  return hipGetLastError();
-}
-template hipError_t launch_cast2<bf16>(const float*, int64_t, int, int, bf16*, int64_t, int, hipStream_t);
-template hipError_t launch_cast2<f16>(const float*, int64_t, int, int, f16*, int64_t, int, hipStream_t);
 
 #define PIGAN_INST(T)                                                                                         \
   template hipError_t launch_first_fwd<T>(int, int, const FirstArgs<T>&, int, hipStream_t);                  \
@@ -1418,7 +1394,7 @@ template hipError_t launch_cast2<f16>(const float*, int64_t, int, int, f16*, int
                                        int, int, hipStream_t);                                                  \
   template hipError_t launch_gp_norm<T>(const float*, int64_t, int, int, const float*, float, double*, int64_t, \
                                         T*, int64_t, int, int, hipStream_t);                                    \
-  template hipError_t launch_cast<T>(const float*, int64_t, int, int, int, T*, T*, int64_t, int, hipStream_t);
+  template hipError_t launch_cast_layers<T>(const CastSet<T>&, const CastSet<T>&, int, hipStream_t);
 PIGAN_INST(float)
 PIGAN_INST(bf16)
 PIGAN_INST(f16)
