@@ -252,7 +252,7 @@ typedef __attribute__((address_space(3))) void* lds_ptr_t;
 // p.kx > 0 (two-term weights): operand X is kx wide, the weight rows are
 // 2 kx wide (without TWO, X is read twice).
 template <class T, int ND1, int ND2, int WM, int WN, int MT, int NT, int EPI, int OCC, bool DB = (OCC >= 2),
-          bool RING = false, int PM = PM_NATIVE, int NB = 2, bool TWO = false>
+          bool RING = false, int PM = PM_NATIVE, int NB = 2, bool TWO = false, int SL = 1>
 __global__ void __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(OCC)))
 k_gemm_nt(const NtArgs<T> p) {
   constexpr int C = 1 + ND1 + ND2;
@@ -263,8 +263,9 @@ k_gemm_nt(const NtArgs<T> p) {
   constexpr int KS = 64 / ES;                      // k values per stage
   constexpr int NCH = 64 / (16 * ES);              // 16-wide chunks per stage
   constexpr int ROWS = C * BM + BN;
-  constexpr int STAGE = ROWS * LDS_PITCH;          // bytes of one operand stage (RING: of one of its two slices)
-  constexpr int PIECES = ROWS * 4;
+  constexpr int SLICE = ROWS * LDS_PITCH;          // bytes of one 64-byte k slice of the operands
+  constexpr int STAGE = SL * SLICE;                // register-staged: SL slices per stage
+  constexpr int PIECES = ROWS * 4 * SL;
   constexpr int PPT = (PIECES + NTH - 1) / NTH;
   constexpr int XBUF = 2 * C * BM * LDS_PITCH, WBUF = 2 * BN * LDS_PITCH;   // RING buffers
   constexpr int OUTB = PM == PM_F64 ? BM * 65 * 4 : 0;   // fp64 products are re-laid out through LDS
@@ -309,7 +310,7 @@ k_gemm_nt(const NtArgs<T> p) {
 #pragma unroll
   for (int i = 0; i < (RING ? 0 : PPT); ++i) {
     const int piece = tid + i * NTH;
-    const int row = piece >> 2, sg = piece & 3;
+    const int row = piece / (4 * SL), sg = piece % (4 * SL);
     valid[i] = UNCOND;
     isx[i] = row < C * BM || piece >= PIECES;   // a dropped re-read stays inside X's first row
     src[i] = Xb;
@@ -378,14 +379,14 @@ k_gemm_nt(const NtArgs<T> p) {
 
   // stage kt of the weights is stage kxs(kt) of operand X (two-term weights
   // read X twice)
-  const int nk = p.K / KS;
-  const int nkx = p.kx > 0 ? p.kx / KS : nk;
+  const int nk = p.K / (KS * SL);
+  const int nkx = p.kx > 0 ? p.kx / (KS * SL) : nk;
   auto kxs = [&](int kt) { return kt >= nkx ? kt - nkx : kt; };
   auto gload = [&](uint4* buf, int kt) {
     const int ktx = kxs(kt);
 #pragma unroll
     for (int i = 0; i < PPT; ++i)
-      buf[i] = (UNCOND || valid[i]) ? *(const uint4*)(src[i] + (int64_t)(isx[i] ? ktx : kt) * 64)
+      buf[i] = (UNCOND || valid[i]) ? *(const uint4*)(src[i] + (int64_t)(isx[i] ? ktx : kt) * (64 * SL))
                                     : make_uint4(0u, 0u, 0u, 0u);
   };
   // PM_SPLIT2: each fp32 value of operand X is cut into its two bf16 pieces
@@ -395,12 +396,12 @@ k_gemm_nt(const NtArgs<T> p) {
   // second the low part.  The weight rows arrive in that layout already (the
   // weight copies are split once per step), and are stored as loaded.
   auto lstore = [&](const uint4* buf, int stage) {
-    char* base = lds + stage * STAGE;
 #pragma unroll
     for (int i = 0; i < PPT; ++i) {
       const int piece = tid + i * NTH;
-      if (piece >= PIECES) continue;
-      const int row = piece >> 2, sg = piece & 3;
+      if (PIECES % NTH != 0 && piece >= PIECES) continue;
+      const int row = piece / (4 * SL), sg = piece & 3;
+      char* base = lds + stage * STAGE + (piece / 4 % SL) * SLICE;
       if (PM == PM_SPLIT2 && row < C * BM) {
         const float* v = (const float*)&buf[i];
         bf16 hi[4], lo[4];
@@ -437,8 +438,7 @@ k_gemm_nt(const NtArgs<T> p) {
   auto piece_at = [&](const char* base, int row, int c) {
     return *(const bf16x8*)(base + row * LDS_PITCH + (((2 * c + (lane >> 5)) ^ gsw) << 4));
   };
-  auto compute = [&](int stage) {
-    const char* base = lds + stage * STAGE;
+  auto compute_slice = [&](const char* base) {
     if constexpr (PM == PM_SPLIT2) {
       bf16x8 bp[NT][2];
 #pragma unroll
@@ -495,6 +495,11 @@ k_gemm_nt(const NtArgs<T> p) {
         }
     }
   };
+  auto compute = [&](int stage) {
+#pragma unroll
+    for (int i = 0; i < SL; ++i) compute_slice(lds + stage * STAGE + i * SLICE);
+  };
+  static_assert(SL == 1 || PM == PM_SPLIT2, "wider stages: split products");
   // PM_F64 (one fragment per wave and stream: 32 points x 32 columns, 2 x 2
   // blocks of the 16 x 16 fp64 product, whose lane l holds rows
   // (l >> 4) + 4 r and column l & 15 of a block)
@@ -2514,35 +2519,49 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
         }
         if (a.N <= 32 && a.pm != PM_F64) {
           dim3 grid((unsigned)(((npts + 127) / 128) * ((a.N + 31) / 32)), 1, G);
-          if (a.pm == PM_SPLIT2) k_gemm_nt<T, ND1, ND2, 4, 1, 1, 1, EPI, 2, true, 0, PM_SPLIT2><<<grid, 256, 0, st>>>(a);
-          else k_gemm_nt<T, ND1, ND2, 4, 1, 1, 1, EPI, 2, true, 0, PM_SPLIT3><<<grid, 256, 0, st>>>(a);
-        } else if (a.pm == PM_SPLIT2 && C == 1 && a.N >= 256 && npts >= 16384) {
-          // 128 points x 256 columns, 4 x 4 waves of 1 x 2 fragments, a ring
-          // of 3 register stages (the fastest measured for the sensor rows
-          // at K = N = 1024)
+          if (a.pm == PM_SPLIT2) k_gemm_nt<T, ND1, ND2, 4, 1, 1, 1, EPI, 2, true, false, PM_SPLIT2><<<grid, 256, 0, st>>>(a);
+          else k_gemm_nt<T, ND1, ND2, 4, 1, 1, 1, EPI, 2, true, false, PM_SPLIT3><<<grid, 256, 0, st>>>(a);
+        } else if (a.pm == PM_SPLIT2 && C == 1 && a.N >= 256 && npts * G >= 16384 && a.K % 32 == 0) {
+          // sensor rows: 128 points x 256 columns, stages of two k slices (a
+          // whole 128-byte line of every row at once).  us per forward launch
+          // at K = N, 262,144 rows (one slice per stage -> two): 1024 1930 ->
+          // 1829 (reverse 1849 -> 1743), 512 592 -> 593 (577 -> 557); at 256
+          // eight waves of 2 x 2 fragments, 229 -> 213 (16 waves of 1 x 2 215
+          // -> 208 in the reverse)
           if constexpr (C == 1) {
             dim3 grid((unsigned)(((npts + 127) / 128) * ((a.N + 255) / 256)), 1, G);
-            k_gemm_nt<T, ND1, ND2, 4, 4, 1, 2, EPI, 1, true, 0, PM_SPLIT2, 3><<<grid, 1024, 0, st>>>(a);
+            if (a.K >= 512) k_gemm_nt<T, ND1, ND2, 4, 4, 1, 2, EPI, 1, true, false, PM_SPLIT2, 3, false, 2><<<grid, 1024, 0, st>>>(a);
+            else if (EPI == EPI_FWD) k_gemm_nt<T, ND1, ND2, 2, 4, 2, 2, EPI, 1, true, false, PM_SPLIT2, 2, false, 2><<<grid, 512, 0, st>>>(a);
+            else k_gemm_nt<T, ND1, ND2, 4, 4, 1, 2, EPI, 1, true, false, PM_SPLIT2, 2, false, 2><<<grid, 1024, 0, st>>>(a);
           }
         } else if (a.pm == PM_SPLIT2 && C == 1 && a.N <= 128) {
-          // 64 points x 128 columns, 2 x 2 waves (no idle column half at N = 128)
+          // no idle column half at N = 128: 64 points x 128 columns, 2 x 2
+          // waves; 128 points and whole-line stages where the arrays outgrow
+          // the memory-side cache (us per launch at K = 128, 131,072 rows:
+          // 42.0 against 45.1, reverse 40.2 against 40.4; 262,144 rows: 122
+          // against 110, reverse 108 against 99)
           if constexpr (C == 1) {
-            dim3 grid((unsigned)(((npts + 63) / 64) * ((a.N + 127) / 128)), 1, G);
-            k_gemm_nt<T, ND1, ND2, 2, 2, 1, 2, EPI, 2, true, 0, PM_SPLIT2><<<grid, 256, 0, st>>>(a);
+            if (a.N == 128 && npts * G >= 196608 && a.K % 32 == 0) {
+              dim3 grid((unsigned)((npts + 127) / 128), 1, G);
+              k_gemm_nt<T, ND1, ND2, 2, 2, 2, 2, EPI, 2, true, false, PM_SPLIT2, 2, false, 2><<<grid, 256, 0, st>>>(a);
+            } else {
+              dim3 grid((unsigned)(((npts + 63) / 64) * ((a.N + 127) / 128)), 1, G);
+              k_gemm_nt<T, ND1, ND2, 2, 2, 1, 2, EPI, 2, true, false, PM_SPLIT2><<<grid, 256, 0, st>>>(a);
+            }
           }
         } else if (a.pm == PM_SPLIT2) {
           // 64 points x 64 NTM columns, 2 x 2 waves
           constexpr int BN = 64 * NTM;
           dim3 grid((unsigned)(((npts + 63) / 64) * ((a.N + BN - 1) / BN)), 1, G);
-          k_gemm_nt<T, ND1, ND2, 2, 2, 1, NTM, EPI, 2, true, 0, PM_SPLIT2><<<grid, 256, 0, st>>>(a);
+          k_gemm_nt<T, ND1, ND2, 2, 2, 1, NTM, EPI, 2, true, false, PM_SPLIT2><<<grid, 256, 0, st>>>(a);
         } else if (a.pm == PM_F64) {
           // fp64 products: 64 x 64 tiles
           dim3 grid((unsigned)(((npts + 63) / 64) * ((a.N + 63) / 64)), 1, G);
-          k_gemm_nt<T, ND1, ND2, 2, 2, 1, 1, EPI, 2, true, 0, PM_F64><<<grid, 256, 0, st>>>(a);
+          k_gemm_nt<T, ND1, ND2, 2, 2, 1, 1, EPI, 2, true, false, PM_F64><<<grid, 256, 0, st>>>(a);
         } else {
           // fp64 stage sums: 64 x 64 tiles
           dim3 grid((unsigned)(((npts + 63) / 64) * ((a.N + 63) / 64)), 1, G);
-          k_gemm_nt<T, ND1, ND2, 2, 2, 1, 1, EPI, 2, true, 0, PM_SPLIT3><<<grid, 256, 0, st>>>(a);
+          k_gemm_nt<T, ND1, ND2, 2, 2, 1, 1, EPI, 2, true, false, PM_SPLIT3><<<grid, 256, 0, st>>>(a);
         }
         return hipGetLastError();
       } else {
