@@ -564,11 +564,13 @@ static void colloc_weights(NtArgs<T>& a, void* ws, const NetBuf& nb, int l) {
 }
 
 // Forward of one generator over a chunk: sensor rows, then (unless colloc is
-// false: a critic-only step of the paired or trunk generators) collocation rows.
+// false: a critic-only step of the paired or trunk generators) collocation
+// rows.  keep: store the pre-activations (no reverse pass reads those of a
+// critic-only step: a third of the sensor rows' traffic).
 template <class T>
 static pigan_status gen_chunk_fwd(void* ws, const NetBuf& nb, const float* params, const float* xs, int64_t xs_g,
                                   const float* xc, int64_t xc_g, const float* z, int64_t z_g, int d, int n_z, int Sc,
-                                  int P, int G, hipStream_t st, bool colloc = true) {
+                                  int P, int G, hipStream_t st, bool colloc = true, bool keep = true) {
   const int W = nb.off.W, L = nb.off.L;
   const int64_t pg = nb.off.n;
   const int64_t ags = nb.Rs * W, agc = nb.Rc * W;   // per-group element strides of the activations
@@ -582,7 +584,7 @@ static pigan_status gen_chunk_fwd(void* ws, const NetBuf& nb, const float* param
     FirstArgs<float> fa{};
     fa.p1 = params; fa.p_g = pg; fa.in_dim = nb.off.in_dim; fa.d = d; fa.W = W;
     fa.zp = tp<float>(ws, nb.zp); fa.zp_g = (int64_t)Sc * W;
-    fa.out_a = tp<float>(ws, nb.As[1]); fa.out_h = tp<float>(ws, nb.Hs[1]); fa.o_g = ags; fa.ldo = W;
+    fa.out_a = keep ? tp<float>(ws, nb.As[1]) : nullptr; fa.out_h = tp<float>(ws, nb.Hs[1]); fa.o_g = ags; fa.ldo = W;
     fa.x = xs; fa.x_g = xs_g; fa.x_shared = 1; fa.Pn = nb.n_s;
     fa.seg = Seg{nb.n_sen, 0, 0};
     fa.exact = adv_pm<T>() == PM_F64;
@@ -594,7 +596,7 @@ static pigan_status gen_chunk_fwd(void* ws, const NetBuf& nb, const float* param
     a.X = tp<float>(ws, nb.Hs[l - 1]); a.x_g = ags; a.ldx = W;
     a.Wm = tp<float>(ws, nb.ws) + (size_t)(l - 2) * W * W; a.w_g = (int64_t)std::max(L - 1, 1) * W * W; a.ldw = W;
     a.bias = params + nb.off.b[l]; a.b_g = pg;
-    a.out_a = tp<float>(ws, nb.As[l]); a.out_h = tp<float>(ws, nb.Hs[l]); a.o_g = ags; a.ldo = W;
+    a.out_a = keep ? tp<float>(ws, nb.As[l]) : nullptr; a.out_h = tp<float>(ws, nb.Hs[l]); a.o_g = ags; a.ldo = W;
     if (nb.skip && trunk_skip(l)) a.skip = tp<float>(ws, nb.Hs[l - 2]);   // residual block output
     a.N = W; a.K = W; a.pm = adv_pm<T>();
     a.seg = Seg{nb.n_sen, 0, 0};
@@ -618,7 +620,7 @@ static pigan_status gen_chunk_fwd(void* ws, const NetBuf& nb, const float* param
     FirstArgs<T> fa{};
     fa.p1 = params; fa.p_g = pg; fa.in_dim = nb.off.in_dim; fa.d = d; fa.W = W;
     fa.zp = tp<float>(ws, nb.zp); fa.zp_g = (int64_t)Sc * W;
-    fa.out_a = tp<T>(ws, nb.Ac[1]); fa.out_h = tp<T>(ws, nb.Hc[1]); fa.o_g = agc; fa.ldo = W;
+    fa.out_a = keep ? tp<T>(ws, nb.Ac[1]) : nullptr; fa.out_h = tp<T>(ws, nb.Hc[1]); fa.o_g = agc; fa.ldo = W;
     fa.x = xc; fa.x_g = xc_g; fa.x_shared = 0; fa.Pn = P;
     fa.seg = Seg{nb.n_col, 0, nb.n_col};
     fa.exact = sizeof(T) == 4;
@@ -630,7 +632,7 @@ static pigan_status gen_chunk_fwd(void* ws, const NetBuf& nb, const float* param
     a.X = tp<T>(ws, nb.Hc[l - 1]); a.x_g = agc; a.ldx = W;
     colloc_weights<T>(a, ws, nb, l);
     a.bias = params + nb.off.b[l]; a.b_g = pg;
-    a.out_a = tp<T>(ws, nb.Ac[l]); a.out_h = tp<T>(ws, nb.Hc[l]); a.o_g = agc; a.ldo = W;
+    a.out_a = keep ? tp<T>(ws, nb.Ac[l]) : nullptr; a.out_h = tp<T>(ws, nb.Hc[l]); a.o_g = agc; a.ldo = W;
     if (l == L && resident) {
       a.out_h = nullptr;
       a.y = tp<float>(ws, nb.jet) + nb.n_sen; a.y_g = nb.R; a.wout = params + nb.off.wout; a.wo_g = pg;
@@ -1053,10 +1055,10 @@ static pigan_status run_step(const pigan_step_desc* s, const StepPlan& pl, const
     // generator forward passes (a critic-only step needs the sensor rows only:
     // the residual penalty is a generator term)
     const bool colloc = !s->critic_only;
-    if ((r = gen_chunk_fwd<T>(ws, Yc, pY, xsG, xs_gY, xcc, xc_g, zc, z_g, d, n_z, Sc, P, G, st, colloc)) != PIGAN_OK)
+    if ((r = gen_chunk_fwd<T>(ws, Yc, pY, xsG, xs_gY, xcc, xc_g, zc, z_g, d, n_z, Sc, P, G, st, colloc, colloc)) != PIGAN_OK)
       return r;
     if (!pl.trunk &&
-        (r = gen_chunk_fwd<T>(ws, Uc, pU, xsU, xs_gU, xcc, xc_g, zc, z_g, d, n_z, Sc, P, G, st, colloc)) != PIGAN_OK)
+        (r = gen_chunk_fwd<T>(ws, Uc, pU, xsU, xs_gU, xcc, xc_g, zc, z_g, d, n_z, Sc, P, G, st, colloc, colloc)) != PIGAN_OK)
       return r;
     // the trunk's head cotangents: the residual and the critic fill only
     // their own rows and streams (Y: value and first derivatives at the
@@ -1190,9 +1192,11 @@ static pigan_status run_hier(const pigan_step_desc* s, const StepPlan& pl, const
     const float* zc = z + (int64_t)s0 * n_z;
     const float* xcc = xc + (int64_t)s0 * P * d;
     const NetBuf Yc = chunk_view(pl.Y, Sc, P), Uc = chunk_view(pl.U, Sc, P);
-    if ((r = gen_chunk_fwd<T>(ws, Yc, pY, xsG, xs_gY, xcc, xc_g, zc, z_g, d, n_z, Sc, P, 1, st)) != PIGAN_OK) return r;
+    const bool keep = !s->critic_only;
+    if ((r = gen_chunk_fwd<T>(ws, Yc, pY, xsG, xs_gY, xcc, xc_g, zc, z_g, d, n_z, Sc, P, 1, st, true, keep)) != PIGAN_OK)
+      return r;
     if (!pl.trunk &&
-        (r = gen_chunk_fwd<T>(ws, Uc, pU, xsU, xs_gU, xcc, xc_g, zc, z_g, d, n_z, Sc, P, 1, st)) != PIGAN_OK)
+        (r = gen_chunk_fwd<T>(ws, Uc, pU, xsU, xs_gU, xcc, xc_g, zc, z_g, d, n_z, Sc, P, 1, st, true, keep)) != PIGAN_OK)
       return r;
     // the u outputs and their cotangents: the trunk's second head, or the u network
     const float* jetU = pl.trunk ? tp<float>(ws, Yc.jet2) : tp<float>(ws, Uc.jet);
