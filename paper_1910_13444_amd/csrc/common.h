@@ -168,6 +168,10 @@ template <class T> struct NtArgs {
   const float* bias; int64_t b_g;         // EPI_FWD: bias on stream 0
   T* out_a;  T* out_h; int64_t o_g; int64_t ldo;  // EPI_FWD: pre-activation / activation
   const T* aprev;                          // EPI_BWD: saved pre-activation of the layer below
+  // EPI_BWD: aprev is the first layer's, whose derivative streams are the same
+  // in every row (columns of W1, zeros): stream k > 0 is the single row
+  // row0 + plane + k - 1
+  int32_t a_seeds;
   T* out_da;                               // EPI_BWD: its pre-activation cotangent
   float* seedY; float* seedU; int64_t sY_g; int64_t sU_g;  // EPI_DF outputs
   int32_t nY; int32_t nU; float df_sign;

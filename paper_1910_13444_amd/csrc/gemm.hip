@@ -340,13 +340,16 @@ k_gemm_nt(const NtArgs<T> p) {
   auto fpt = [&](int u, int j) { return m0 + 32 * (MT * wm + u) + (lane & 15) + 16 * j; };
   // the pieces of fragment (u, t) of stream k of an array laid out as the
   // outputs; points past the segment end and columns past N take valid elements
-  auto load_frag = [&](FragRaw<T>& f, const T* base, int u, int k, int t) {
+  // (one_row: the stream's single row, a_seeds)
+  auto load_frag = [&](FragRaw<T>& f, const T* base, int u, int k, int t, bool one_row = false) {
     const int nb = fcol(t) < p.N ? fcol(t) : 0;
+    const int64_t row0 = p.seg.row0 + (one_row ? p.seg.plane + k - 1 : k * p.seg.plane);
+    const int64_t pmask = one_row ? 0 : -1;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       int64_t pt = fpt(u, j);
       if (pt > npts - 1) pt = npts - 1;
-      const T* row = base + g * p.o_g + (p.seg.row0 + k * p.seg.plane + pt) * p.ldo + nb;
+      const T* row = base + g * p.o_g + (row0 + (pt & pmask)) * p.ldo + nb;
 #pragma unroll
       for (int i = 0; i < (ES == 2 ? 1 : 2); ++i) f.w[i][j] = *(const u32x4*)(row + frag_col<T>(lane, i));
     }
@@ -363,7 +366,7 @@ k_gemm_nt(const NtArgs<T> p) {
 #pragma unroll
       for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int k = 0; k < C; ++k) load_frag(apre[u][k][t], p.aprev, u, k, t);
+        for (int k = 0; k < C; ++k) load_frag(apre[u][k][t], p.aprev, u, k, t, k > 0 && p.a_seeds);
     __builtin_amdgcn_sched_barrier(0);
   }
 
@@ -841,9 +844,9 @@ k_gemm_nt(const NtArgs<T> p) {
       }
     }
   };
-  auto load_rows = [&](FragRaw<T>* raw, const T* src, int u, int t) {
+  auto load_rows = [&](FragRaw<T>* raw, const T* src, int u, int t, bool seeds = false) {
 #pragma unroll
-    for (int k = 0; k < C; ++k) load_frag(raw[k], src, u, k, t);
+    for (int k = 0; k < C; ++k) load_frag(raw[k], src, u, k, t, k > 0 && seeds);
     __builtin_amdgcn_sched_barrier(0);   // all in flight together
   };
   auto add_rows = [&](FragRaw<T>* raw, int u, int t) {
@@ -926,7 +929,7 @@ k_gemm_nt(const NtArgs<T> p) {
         add_rows(sk, u, t);
       }
       FragRaw<T> raw[PRE ? 1 : C];
-      if constexpr (!PRE) load_rows(raw, p.aprev, u, t);
+      if constexpr (!PRE) load_rows(raw, p.aprev, u, t, p.a_seeds);
       if (p.out_gh) store_rows(p.out_gh, u, t);
 #pragma unroll
       for (int k = 0; k < C; ++k) {
@@ -1524,10 +1527,13 @@ k_gemm_nt_wr(const NtArgs<T> p, int64_t ntiles) {
       const uint32_t po = (uint32_t)(pt * p.ldo * ES);
 #pragma unroll
       for (int k = 0; k < C; ++k) {
-        const char* base = (const char*)(p.aprev + g * p.o_g + (p.seg.row0 + k * p.seg.plane) * p.ldo);
+        const bool one_row = SKIP && k > 0 && p.a_seeds;   // (launches without a skip have whole streams)
+        const char* base = (const char*)(p.aprev + g * p.o_g +
+                                         (p.seg.row0 + (one_row ? p.seg.plane + k - 1 : k * p.seg.plane)) * p.ldo);
+        const uint32_t pk = one_row ? 0u : po;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          apr[k][q] = *(const u32x2*)(base + po + ncol(q) * ES);
+          apr[k][q] = *(const u32x2*)(base + pk + ncol(q) * ES);
         }
       }
     }
@@ -2591,6 +2597,7 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
           return hipGetLastError();
         }
       }
+      if (a.a_seeds && !a.fp1 && !skip) return hipErrorInvalidValue;
       if (a.fp1) k_gemm_nt_wr<T, ND1, ND2, EPI, true><<<grid, 256, 0, st>>>(a, ntiles);
       else if (skip) k_gemm_nt_wr<T, ND1, ND2, EPI, false, true><<<grid, 256, 0, st>>>(a, ntiles);
       else k_gemm_nt_wr<T, ND1, ND2, EPI, false><<<grid, 256, 0, st>>>(a, ntiles);

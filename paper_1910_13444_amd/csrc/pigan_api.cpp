@@ -550,6 +550,12 @@ static void first_src(NtArgs<T>& a, const float* params, int64_t pg, int in_dim,
   a.fzp = zp; a.fzp_g = zp_g;
 }
 
+// whether the first layer's derivative pre-activations are stored as one row
+// per stream (NtArgs::a_seeds): not where the output pass reads them (a single
+// layer), nor in a two-layer trunk (no residual block: the resident kernel
+// without a skip reads whole streams)
+static bool first_seeds(const NetBuf& nb) { return nb.off.L >= (nb.skip ? 3 : 2); }
+
 // collocation forward weights of hidden layer l: two-term rows [W_hi | W_lo]
 // in 16-bit storage
 template <class T>
@@ -621,10 +627,12 @@ static pigan_status gen_chunk_fwd(void* ws, const NetBuf& nb, const float* param
     fa.p1 = params; fa.p_g = pg; fa.in_dim = nb.off.in_dim; fa.d = d; fa.W = W;
     fa.zp = tp<float>(ws, nb.zp); fa.zp_g = (int64_t)Sc * W;
     fa.out_a = keep ? tp<T>(ws, nb.Ac[1]) : nullptr; fa.out_h = tp<T>(ws, nb.Hc[1]); fa.o_g = agc; fa.ldo = W;
+    fa.a_seeds = first_seeds(nb);
     fa.x = xc; fa.x_g = xc_g; fa.x_shared = 0; fa.Pn = P;
     fa.seg = Seg{nb.n_col, 0, nb.n_col};
     fa.exact = sizeof(T) == 4;
-    ProfScope ps(st, "first_fwd", 2.0 * nb.n_col * W * d * G, (double)mc * W * 2 * sizeof(T) * G);
+    ProfScope ps(st, "first_fwd", 2.0 * nb.n_col * W * d * G,
+                 (double)(mc + (fa.a_seeds ? nb.n_col : mc)) * W * sizeof(T) * G);
     HIP_TRY(launch_first_fwd<T>(nb.nd1, nb.nd2, fa, G, st));
   }
   for (int l = 2; l <= L; ++l) {
@@ -754,6 +762,7 @@ static pigan_status gen_chunk_bwd(void* ws, const StepPlan& pl, const NetBuf& nb
     ac.X = tp<T>(ws, nb.dAc[cur]); ac.x_g = agc; ac.ldx = W;
     ac.Wm = tp<T>(ws, nb.wcT) + (size_t)(l - 2) * W * W; ac.w_g = (int64_t)std::max(L - 1, 1) * W * W; ac.ldw = W;
     ac.aprev = tp<T>(ws, nb.Ac[l - 1]); ac.out_da = tp<T>(ws, nb.dAc[1 - cur]); ac.o_g = agc; ac.ldo = W;
+    ac.a_seeds = l == 2 && first_seeds(nb);
     if (l == 2 && resident)   // the first layer's pre-activations were never stored
       first_src(ac, params, pg, nb.off.in_dim, d, tp<float>(ws, nb.zp), (int64_t)Sc * W);
     if (skip_in) ac.skip_g = tp<T>(ws, nb.ghc);

@@ -9,6 +9,7 @@ template <class T> struct FirstArgs {
   const float* zp; int64_t zp_g;                           // per-sample z-projection + b1
   const float* x; int64_t x_g; int x_shared; int64_t Pn;   // locations; Pn points per sample
   T* out_a; T* out_h; int64_t o_g; int64_t ldo;
+  int a_seeds;                                             // derivative streams of out_a: one row each (NtArgs::a_seeds)
   Seg seg;
   int exact;                                               // fp32 storage: tanh in fp64
 };

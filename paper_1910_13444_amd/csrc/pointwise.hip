@@ -121,11 +121,19 @@ k_first_fwd(FirstArgs<T> p) {
       const int64_t base = g * p.o_g + (p.seg.row0 + pt) * p.ldo + n0;
       if (p.out_a) {
         store8<T>(p.out_a + base, a);
+        // the derivative streams of a_1 are the same in every row: with
+        // a_seeds the first point alone writes them, to the rows after plane
+        // (they were 8 of the 10 planes stored by five streams: 470 -> 300 us
+        // at W = 512, 256,064 points, and as much to read back)
+        if (!p.a_seeds || pt == 0) {
+          const int64_t st = p.a_seeds ? p.ldo : pl;
+          T* o = p.out_a + base + pl;              // (pt == 0: row0 + plane)
 #pragma unroll
-        for (int i = 0; i < ND1; ++i) store8<T>(p.out_a + base + (1 + i) * pl, wc[i]);
-        float z8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+          for (int i = 0; i < ND1; ++i) store8<T>(o + i * st, wc[i]);
+          float z8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-        for (int i = 0; i < ND2; ++i) store8<T>(p.out_a + base + (1 + ND1 + i) * pl, z8);
+          for (int i = 0; i < ND2; ++i) store8<T>(o + (ND1 + i) * st, z8);
+        }
       }
 #pragma unroll
       for (int k = 0; k < C; ++k) store8<T>(p.out_h + base + k * pl, h[k]);
