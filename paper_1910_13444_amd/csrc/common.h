@@ -176,9 +176,12 @@ template <class T> struct NtArgs {
   float* seedY; float* seedU; int64_t sY_g; int64_t sU_g;  // EPI_DF outputs
   int32_t nY; int32_t nU; float df_sign;
   // EPI_FWD of the last hidden layer with the output layer fused (only where
-  // nt_resident_ok holds): y[row] = w_out . h (+ b_out on the value stream),
+  // nt_resident_ok or nt_ring_out_ok holds): y[row] = w_out . h (+ b_out on the value stream),
   // rows in the activation row layout; wout = [w_out (N), b_out]
   float* y; int64_t y_g; const float* wout; int64_t wo_g;
+  // the ring kernels' fused output layer: out_h is not written; sums of 128
+  // columns go to ypart (yp_g floats per group, at least N / 128 per row)
+  float* ypart; int64_t yp_g;
   // second-layer calls with the first layer formed in the kernel (only where
   // nt_resident_ok holds; fp1 != null): the forward builds its operand X,
   // and the reverse pass its saved pre-activations, from the coordinates, the
@@ -232,6 +235,10 @@ hipError_t launch_gemm_dw(const T* dA, int64_t a_g, int64_t lda, const T* H, int
 // storage, K = N = 128, at most 5 streams, rows addressable with 32-bit
 // offsets)
 bool nt_resident_ok(int elem_bytes, int C, int K, int N, int64_t n_points, int64_t ldx, int64_t ldo);
+
+// whether launch_gemm_nt runs this shape's forward on the ring kernels, which
+// can fuse the output layer too (16-bit storage, two-term weights)
+bool nt_ring_out_ok(int elem_bytes, int C, int K, int N, int64_t n_points);
 
 void dw_split_plan(int64_t R, int N, int J, int elem_bytes, int G, int* n_split, int64_t* rows_per_split);
 

@@ -26,9 +26,10 @@
 // block is WM x WN waves.  The MFMA computes W . X^T so that a lane holds one
 // point and runs of four columns (vector stores, lane-local derivative
 // carry).  Operands are staged through LDS in 64-byte k-slices (swizzled
-// segments, conflict-free writes and fragment reads): wide layers load them
-// straight into a 3- or 4-deep LDS ring, the others prefetch the next slices
-// into registers while the current one is multiplied.
+// segments, conflict-free writes and fragment reads): 16-bit layers of 128
+// columns and more load them straight into LDS, two slices (a whole 128-byte
+// line of every row) per stage, the others prefetch the next slices into
+// registers while the current one is multiplied.
 #include "common.h"
 
 namespace pigan {
@@ -247,12 +248,16 @@ typedef __attribute__((address_space(3))) void* lds_ptr_t;
 // for single 64-byte slices, 34.8 TB/s in pairs).
 // TWO (with RING): two-term weights.  A k slice of X is staged once and used
 // by two stages of weights, the low terms and the high terms.
+// OUT (with TWO): the output layer fused in place of the activations' store,
+// which took one write and one read of every top activation (whole steps of
+// 16 x 256-wide, 512-wide and 1024-wide generators 63.9 -> 62.4, 36.2 -> 35.8
+// and 164.1 -> 163.5 ms).
 // PM (fp32 storage only): products from bf16 pieces of the fp32 operands
 // (ProdMode); PM_SPLIT3 folds the accumulators into fp64 after every stage.
 // p.kx > 0 (two-term weights): operand X is kx wide, the weight rows are
 // 2 kx wide (without TWO, X is read twice).
 template <class T, int ND1, int ND2, int WM, int WN, int MT, int NT, int EPI, int OCC, bool DB = (OCC >= 2),
-          bool RING = false, int PM = PM_NATIVE, int NB = 2, bool TWO = false, int SL = 1>
+          bool RING = false, int PM = PM_NATIVE, int NB = 2, bool TWO = false, int SL = 1, bool OUT = false>
 __global__ void __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(OCC)))
 k_gemm_nt(const NtArgs<T> p) {
   constexpr int C = 1 + ND1 + ND2;
@@ -272,6 +277,7 @@ k_gemm_nt(const NtArgs<T> p) {
   constexpr int LDSB = RING ? 2 * (XBUF + WBUF) : (2 * STAGE > OUTB ? 2 * STAGE : OUTB);
   static_assert(!RING || (ES == 2 && PM == PM_NATIVE), "direct-to-LDS stages: 16-bit types");
   static_assert(PM == PM_NATIVE || ES == 4, "split products: fp32 storage");
+  static_assert(!OUT || TWO, "fused output layer: two-term ring kernels");
   static_assert(!TWO || (RING && EPI == EPI_FWD), "two-term stages: ring kernels, forward products");
   // fp32 mode (fp32 storage, products not split into bf16): tanh in fp64
   constexpr bool X64 = ES == 4 && PM != PM_SPLIT2 && PM != PM_SPLIT3;
@@ -869,6 +875,9 @@ k_gemm_nt(const NtArgs<T> p) {
     // (all biases of a lane are read together: behind a check of its own, each
     // of the up to 32 loads was waited for by itself, about a third of a
     // block's time at K = 512)
+    // fused output layer: w_out . h over the lane's columns, the activations
+    // as stored
+    float ys[OUT ? MT : 1][OUT ? C : 1][OUT ? NT : 1];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       float bv[16];
@@ -885,7 +894,7 @@ k_gemm_nt(const NtArgs<T> p) {
         // (the residual rows are read ahead of the tanh where they fit)
         constexpr bool AHEAD = MT * C * NT * 16 < 160;
         FragRaw<T> sk[AHEAD ? C : 1];
-        if constexpr (AHEAD) {
+        if constexpr (AHEAD && !OUT) {
           if (p.skip) load_rows(sk, p.skip, u, t);
         }
         if (p.out_a) store_rows(p.out_a, u, t);
@@ -899,18 +908,60 @@ k_gemm_nt(const NtArgs<T> p) {
           for (int k = 0; k < C; ++k) acc[u][k][t][r] = v[k];
           if (MT * C * NT * 16 >= 160 && r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
-        // residual block output: h_l = tanh carry + h_{l-2}, stream by stream
-        if (p.skip) {
-          if constexpr (AHEAD) {
-            add_rows(sk, u, t);
-          } else {
-            FragRaw<T> late[C];
-            load_rows(late, p.skip, u, t);
-            add_rows(late, u, t);
+        if constexpr (OUT) {
+          // (N is a multiple of 128: whole fragments)
+          const float* wp = p.wout + g * p.wo_g + (fcol(t) < p.N ? fcol(t) : 0) + 4 * hh;
+          float wo[16];
+#pragma unroll
+          for (int r = 0; r < 16; ++r) wo[r] = wp[8 * (r >> 2) + (r & 3)];
+#pragma unroll
+          for (int k = 0; k < C; ++k) {
+            float v = 0.0f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v += wo[r] * Elem<T>::to_f(Elem<T>::from_f(acc[u][k][t][r]));
+            ys[u][k][t] = v;
           }
+        } else {
+          // residual block output: h_l = tanh carry + h_{l-2}, stream by stream
+          if (p.skip) {
+            if constexpr (AHEAD) {
+              add_rows(sk, u, t);
+            } else {
+              FragRaw<T> late[C];
+              load_rows(late, p.skip, u, t);
+              add_rows(late, u, t);
+            }
+          }
+          store_rows(p.out_h, u, t);
         }
-        store_rows(p.out_h, u, t);
         __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if constexpr (OUT) {
+      // the lane halves, then the four fragments of each 128 columns in column
+      // order, whatever waves and tiles hold them: the result does not depend
+      // on the tile shape.  k_out_sum adds the groups of 128.
+      float* red = (float*)lds;                    // [BN / 32][C][BM]
+      lds_sync();                                  // the stages have been read
+#pragma unroll
+      for (int u = 0; u < MT; ++u)
+#pragma unroll
+        for (int k = 0; k < C; ++k)
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            const float v = ys[u][k][t] + __shfl_xor(ys[u][k][t], 32);
+            if (hh == 0) red[((wn * NT + t) * C + k) * BM + mloc(u)] = v;
+          }
+      lds_sync();
+      const int groups = p.N / 128;
+      for (int i = tid; i < (BN / 128) * C * BM; i += NTH) {
+        const int gr = i / (C * BM), k = i / BM % C;
+        const int64_t pt = m0 + i % BM;
+        const float* f = red + (int64_t)gr * 4 * C * BM + i % (C * BM);
+        const float v = ((f[0] + f[C * BM]) + f[2 * C * BM]) + f[3 * C * BM];
+        if (pt >= npts || n0 / 128 + gr >= groups) continue;
+        if (groups == 1) p.y[g * p.y_g + p.seg.row0 + k * p.seg.plane + pt] = k == 0 ? v + p.wout[g * p.wo_g + p.N] : v;
+        else p.ypart[g * p.yp_g + (int64_t)(n0 / 128 + gr) * C * npts + k * npts + pt] = v;
       }
     }
     return;
@@ -965,6 +1016,22 @@ k_gemm_nt(const NtArgs<T> p) {
       __builtin_amdgcn_sched_barrier(0);
     }
   }
+}
+
+// fused output layer over several groups of 128 columns: y = the groups' sums
+// in order (+ b_out on the value stream)
+__global__ void __launch_bounds__(256)
+k_out_sum(const float* __restrict__ part, int64_t part_g, int groups, int64_t npts, int C, Seg seg,
+          const float* __restrict__ wout, int64_t wo_g, int N, float* __restrict__ y, int64_t y_g) {
+  const int g = blockIdx.z;
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= C * npts) return;
+  const float* p = part + g * part_g + i;
+  float v = p[0];
+  for (int t = 1; t < groups; ++t) v += p[(int64_t)t * C * npts];
+  const int64_t k = i / npts;
+  if (k == 0) v += wout[g * wo_g + N];
+  y[g * y_g + seg.row0 + k * seg.plane + (i - k * npts)] = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -2467,6 +2534,14 @@ bool nt_resident_ok(int elem_bytes, int C, int K, int N, int64_t n_points, int64
   return elem_bytes == 2 && C >= 1 && C <= 5 && K == 128 && N == 128 && span < ((int64_t)1 << 31);
 }
 
+// (three streams and more: one and two stay on the large tiles, which are
+// slower with the output layer fused: field evaluation of 512-wide generators,
+// value rows only, 8.34 ms fused, 7.17 apart)
+bool nt_ring_out_ok(int elem_bytes, int C, int K, int N, int64_t n_points) {
+  return elem_bytes == 2 && C >= 3 && C <= 7 && K == N && N >= 128 && N % 128 == 0 && n_points > 0 &&
+         !nt_resident_ok(elem_bytes, C, K, N, n_points, K, N);
+}
+
 namespace {
 
 // compute units of the current device (cached per device)
@@ -2604,7 +2679,9 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
       return hipGetLastError();
     }
   }
-  if (a.y || a.fp1) return hipErrorInvalidValue;  // output / first-layer fusion only in the resident kernel
+  // the first layer is fused only in the resident kernel, the output layer in
+  // the ring kernels too
+  if (a.fp1 || (a.y && !(C >= 3 && !a.skip && ring_ok<T, C, EPI>(a) && a.ypart && a.N % 128 == 0))) return hipErrorInvalidValue;
   if constexpr (EPI == EPI_DF) {
     if (a.skip || a.skip_g || a.out_gh) return hipErrorInvalidValue;
   }
@@ -2631,7 +2708,11 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
       constexpr int WM = C == 1 ? 4 : 2, WN = C == 1 ? 2 : 4, MT = C <= 3 && TWO ? 2 : 1, NT = C == 1 ? 4 : (C <= 3 || C == 5 ? 2 : 1);
       constexpr int BM = 32 * MT * WM, BN = 32 * NT * WN;
       const int64_t blocks = ((npts + BM - 1) / BM) * ((a.N + BN - 1) / BN) * G;
-      const bool large = a.N >= 256 && blocks >= 2 * (int64_t)cu_count() && !(C == 5 && (!TWO || a.N == 256)) &&
+      // (with the output layer fused the large tiles take up to twice as long,
+      // five streams at K = 512 1917 us against 1520 on the small one, three
+      // 1854 against 1094: the column weights push the accumulators out of the
+      // register file)
+      const bool large = !a.y && a.N >= 256 && blocks >= 2 * (int64_t)cu_count() && !(C == 5 && (!TWO || a.N == 256)) &&
                          !(C == 3 && !TWO && a.N == 256);
       if constexpr (TWO || C <= 4) {
         if (large) {
@@ -2641,6 +2722,15 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
         }
       }
       dim3 grid((unsigned)(((npts + 31) / 32) * ((a.N + 127) / 128)), 1, G);
+      if constexpr (TWO && C >= 3) {
+        if (a.y) {
+          k_gemm_nt<T, ND1, ND2, 1, 4, 1, 1, EPI, (C <= 5 ? 2 : 1), true, true, PM_NATIVE, 2, TWO, 1, true><<<grid, 256, 0, st>>>(a);
+          if (a.N > 128)
+            k_out_sum<<<dim3((unsigned)((C * npts + 255) / 256), 1, G), 256, 0, st>>>(
+                a.ypart, a.yp_g, a.N / 128, npts, C, a.seg, a.wout, a.wo_g, a.N, a.y, a.y_g);
+          return hipGetLastError();
+        }
+      }
       k_gemm_nt<T, ND1, ND2, 1, 4, 1, 1, EPI, (C <= 5 ? 2 : 1), true, true, PM_NATIVE, 2, TWO><<<grid, 256, 0, st>>>(a);
     } else {
       return hipErrorInvalidValue;

@@ -622,6 +622,8 @@ static pigan_status gen_chunk_fwd(void* ws, const NetBuf& nb, const float* param
   const int C = nb.C();
   const int64_t mc = C * nb.n_col;
   const bool resident = colloc_resident<T>(nb);
+  // wide 16-bit layers: only the output layer is fused
+  const bool fuse_out = L >= 2 && nb.heads == 1 && nt_ring_out_ok((int)sizeof(T), C, W, W, nb.n_col);
   if (!resident) {
     FirstArgs<T> fa{};
     fa.p1 = params; fa.p_g = pg; fa.in_dim = nb.off.in_dim; fa.d = d; fa.W = W;
@@ -645,6 +647,11 @@ static pigan_status gen_chunk_fwd(void* ws, const NetBuf& nb, const float* param
       a.out_h = nullptr;
       a.y = tp<float>(ws, nb.jet) + nb.n_sen; a.y_g = nb.R; a.wout = params + nb.off.wout; a.wo_g = pg;
     }
+    if (l == L && fuse_out) {   // (the top activations are not stored: their buffer holds the tiles' sums)
+      a.out_h = nullptr;
+      a.y = tp<float>(ws, nb.jet) + nb.n_sen; a.y_g = nb.R; a.wout = params + nb.off.wout; a.wo_g = pg;
+      a.ypart = tp<float>(ws, nb.Hc[L]); a.yp_g = agc / 2;
+    }
     if (l == 2 && resident) {
       first_src(a, params, pg, nb.off.in_dim, d, tp<float>(ws, nb.zp), (int64_t)Sc * W);
       a.f_out_h = tp<T>(ws, nb.Hc[1]);
@@ -656,7 +663,7 @@ static pigan_status gen_chunk_fwd(void* ws, const NetBuf& nb, const float* param
     pigan_status s1 = gemm_nt<T>(EPI_FWD, nb.nd1, nb.nd2, a, G, st, "gemm_fwd");
     if (s1 != PIGAN_OK) return s1;
   }
-  if (!resident) {
+  if (!resident && !fuse_out) {
     ProfScope ps(st, "out_fwd", 2.0 * nb.heads * mc * W * G, (double)nb.heads * mc * W * sizeof(T) * G);
     HIP_TRY(launch_out_fwd<T>(tp<T>(ws, nb.Hc[L]), agc, W, mc, nb.n_col, W, params + nb.off.wout, pg,
                               tp<float>(ws, nb.jet) + nb.n_sen, nb.R, G, st));
@@ -1761,9 +1768,10 @@ static pigan_status run_gen_fwd(const pigan_mlp* net, const float* params, int d
   }
   // on the resident kernel the first layer is formed inside the second
   // layer's GEMM and the output layer rides on the last one's epilogue
-  const bool fuse_out = L >= 2 && nt_resident_ok((int)sizeof(T), 1 + nd1 + nd2, W, W, M, W, W);
+  const bool resident = L >= 2 && nt_resident_ok((int)sizeof(T), 1 + nd1 + nd2, W, W, M, W, W);
+  const bool fuse_out = resident || (L >= 2 && nt_ring_out_ok((int)sizeof(T), 1 + nd1 + nd2, W, W, M));
   const int64_t x_g = x_shared ? (int64_t)P * d : M * d;
-  if (!fuse_out) {
+  if (!resident) {
     FirstArgs<T> fa{};
     fa.p1 = params; fa.p_g = off.n; fa.in_dim = in_dim; fa.d = d; fa.W = W;
     fa.zp = tp<float>(ws, p.zp); fa.zp_g = (int64_t)S * W;
@@ -1783,10 +1791,11 @@ static pigan_status run_gen_fwd(const pigan_mlp* net, const float* params, int d
     a.bias = params + off.b[l]; a.b_g = off.n;
     a.out_a = nullptr; a.out_h = tp<T>(ws, p.h[1 - cur]); a.o_g = actg; a.ldo = W;
     if (l == L && fuse_out) {
+      a.ypart = tp<float>(ws, p.h[1 - cur]); a.yp_g = actg / 2;   // (the ring kernels' tile sums)
       a.out_h = nullptr;
       a.y = jet; a.y_g = p.R; a.wout = params + off.wout; a.wo_g = off.n;
     }
-    if (l == 2 && fuse_out) {
+    if (l == 2 && resident) {
       first_src(a, params, off.n, in_dim, d, tp<float>(ws, p.zp), (int64_t)S * W);
       a.fx = x; a.fx_g = x_g; a.fx_shared = x_shared ? 1 : 0; a.fPn = P;
     }
