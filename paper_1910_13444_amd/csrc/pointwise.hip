@@ -9,21 +9,49 @@
 namespace pigan {
 
 // ---------------------------------------------------------------------------
-// zp[g][s][n] = b1[n] + sum_j W1[n][d + j] z[g][s][j]   (summed in fp64,
-// stored in fp32)
+// zp[g][s][n] = b1[n] + sum_j W1[n][d + j] z[g][s][j]   (summed in fp64, in the
+// order of j, stored in fp32)
+// A block takes 32 columns x 8 samples and stages ZP_J of the sum's terms in
+// LDS: with every thread reading its own row of W1 a lane waited for each
+// cache line by itself (256 columns, 16 groups, 128 samples of 32 inputs:
+// 70.4 us, here 6.2; 1024 columns, 96 samples of 128 inputs 37.8 and 7.3).
 // ---------------------------------------------------------------------------
-__global__ void k_zproj(const float* __restrict__ p1, int64_t p_g, int in_dim, int d, int W,
-                        const float* __restrict__ z, int64_t z_g, int n_z, int S, float* __restrict__ zp,
-                        int64_t zp_g) {
-  const int g = blockIdx.z;
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (int64_t)S * W) return;
-  const int s = (int)(idx / W), n = (int)(idx % W);
-  const float* Wn = p1 + g * p_g + (int64_t)n * in_dim + d;
-  const float* zs = z + g * z_g + (int64_t)s * n_z;
-  double a = (double)p1[g * p_g + (int64_t)W * in_dim + n];
-  for (int j = 0; j < n_z; ++j) a += (double)Wn[j] * (double)zs[j];
-  zp[g * zp_g + idx] = (float)a;
+constexpr int ZP_J = 64;
+__global__ void __launch_bounds__(256)
+k_zproj(const float* __restrict__ p1, int64_t p_g, int in_dim, int d, int W, const float* __restrict__ z, int64_t z_g,
+        int n_z, int S, float* __restrict__ zp, int64_t zp_g) {
+  __shared__ float wt[32][ZP_J + 1], zt[8][ZP_J];
+  const int g = blockIdx.z, tid = threadIdx.x;
+  const int nt = (W + 31) / 32;
+  const int n0 = (int)(blockIdx.x % nt) * 32, s0 = (int)(blockIdx.x / nt) * 8;
+  const int n = n0 + (tid & 31), s = s0 + (tid >> 5);
+  const float* Wg = p1 + g * p_g + d;
+  const float* zg = z + g * z_g;
+  double a = n < W ? (double)p1[g * p_g + (int64_t)W * in_dim + n] : 0.0;
+  for (int j0 = 0; j0 < n_z; j0 += ZP_J) {
+    const int j = j0 + tid % ZP_J, r = tid / ZP_J;
+    float wv[32 * ZP_J / 256], zv[8 * ZP_J / 256];
+#pragma unroll
+    for (int i = 0; i < 32 * ZP_J / 256; ++i) {
+      const int row = n0 + r + i * (256 / ZP_J);
+      wv[i] = j < n_z && row < W ? Wg[(int64_t)row * in_dim + j] : 0.0f;
+    }
+#pragma unroll
+    for (int i = 0; i < 8 * ZP_J / 256; ++i) {
+      const int row = s0 + r + i * (256 / ZP_J);
+      zv[i] = j < n_z && row < S ? zg[(int64_t)row * n_z + j] : 0.0f;
+    }
+    __syncthreads();                               // the last terms have been read
+#pragma unroll
+    for (int i = 0; i < 32 * ZP_J / 256; ++i) wt[r + i * (256 / ZP_J)][tid % ZP_J] = wv[i];
+#pragma unroll
+    for (int i = 0; i < 8 * ZP_J / 256; ++i) zt[r + i * (256 / ZP_J)][tid % ZP_J] = zv[i];
+    __syncthreads();
+    const int m = n_z - j0 < ZP_J ? n_z - j0 : ZP_J;
+#pragma unroll 8
+    for (int q = 0; q < m; ++q) a += (double)wt[tid & 31][q] * (double)zt[tid >> 5][q];
+  }
+  if (n < W && s < S) zp[g * zp_g + (int64_t)s * W + n] = (float)a;
 }
 
 // ---------------------------------------------------------------------------
@@ -1058,12 +1086,18 @@ __global__ void __launch_bounds__(256) k_cast_layers(const CastSet<T> c0, const 
   const int N = c.N, K = c.K, Kp = c.Kp;
   const float* src = c.src + g * c.s_g + l * c.s_l;
   const int64_t o = g * c.d_g + (int64_t)l * N * Kp;
+  // (read together: behind a row's stores each read was waited for by itself)
+  float vs[4];
 #pragma unroll
-  for (int r = ty; r < 32; r += 8) {
-    const int n = n0 + r, k = k0 + tx;
-    float v = 0.0f;
+  for (int i = 0; i < 4; ++i) {
+    const int n = n0 + ty + 8 * i, k = k0 + tx;
+    vs[i] = n < N && k < K ? src[(int64_t)n * K + k] : 0.0f;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = ty + 8 * i, n = n0 + r, k = k0 + tx;
+    const float v = vs[i];
     if (n < N && k < Kp) {
-      v = k < K ? src[(int64_t)n * K + k] : 0.0f;
       const int64_t e = o + (int64_t)n * Kp + k;
       if (c.two) {
         const T hi = Elem<T>::from_f(v);
@@ -1101,7 +1135,9 @@ static inline unsigned nblk(int64_t n, int b) { return (unsigned)((n + b - 1) / 
 
 hipError_t launch_zproj(const float* p1, int64_t p_g, int in_dim, int d, int W, const float* z, int64_t z_g,
                         int n_z, int S, float* zp, int64_t zp_g, int G, hipStream_t st) {
-  k_zproj<<<dim3(nblk((int64_t)S * W, 256), 1, G), 256, 0, st>>>(p1, p_g, in_dim, d, W, z, z_g, n_z, S, zp, zp_g);
+  const int64_t blocks = (int64_t)nblk(W, 32) * nblk(S, 8);
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  k_zproj<<<dim3((unsigned)blocks, 1, G), 256, 0, st>>>(p1, p_g, in_dim, d, W, z, z_g, n_z, S, zp, zp_g);
   return hipGetLastError();
 }
 

@@ -73,3 +73,21 @@ def test_disc_forward_short(dtype, G, B, n_in, L, W):
     for g in range(G):
         ref = oracle.mlp_forward(p[g], shape, snap[g])
         check({f"g{g}": rel(sc[g], ref)}, TOL[dtype], f"disc_forward short {dtype}")
+
+
+# latent part of the first layer: blocks of 32 columns x 8 samples, 64 terms at
+# a time
+@pytest.mark.parametrize("S,n_z,W", [(1, 1, 32), (9, 63, 64), (7, 64, 128), (8, 65, 32), (17, 130, 256)])
+def test_gen_forward_latent_sum(S, n_z, W):
+    import torch
+    print(f"gen_forward latent S={S} n_z={n_z} W={W}", flush=True)
+    rng = np.random.default_rng(S + n_z)
+    shape = (1 + n_z, 2, W)
+    p = glorot_mlp(rng, *shape)[None]
+    z = rng.standard_normal((1, S, n_z)).astype(np.float32)
+    x = rng.random((1, S, 3, 1)).astype(np.float32)
+    got = pigan.gen_forward(to_dev(p), shape, 1, to_dev(z), to_dev(x), 1, dtype="fp32")
+    torch.cuda.synchronize()
+    got = got.cpu().numpy()[0]
+    ref = oracle.gen_jets(p[0], shape, 1, z[0], x[0], 1)
+    check({f"c{k}": rel(got[k], ref[k]) for k in range(ref.shape[0])}, TOL["fp32"], f"latent S={S} n_z={n_z} W={W}")
