@@ -246,18 +246,19 @@ typedef __attribute__((address_space(3))) void* lds_ptr_t;
 // two 64-byte slices back to back: a cache line then crosses from L2 once
 // (measured with every block reading L2-resident rows: 18.3 TB/s over the chip
 // for single 64-byte slices, 34.8 TB/s in pairs).
-// TWO (with RING): two-term weights.  A k slice of X is staged once and used
-// by two stages of weights, the low terms and the high terms.
-// OUT (with TWO): the output layer fused in place of the activations' store,
+// OUT (with RING): the output layer fused in place of the activations' store,
 // which took one write and one read of every top activation (whole steps of
 // 16 x 256-wide, 512-wide and 1024-wide generators 63.9 -> 62.4, 36.2 -> 35.8
 // and 164.1 -> 163.5 ms).
 // PM (fp32 storage only): products from bf16 pieces of the fp32 operands
 // (ProdMode); PM_SPLIT3 folds the accumulators into fp64 after every stage.
-// p.kx > 0 (two-term weights): operand X is kx wide, the weight rows are
-// 2 kx wide (without TWO, X is read twice).
+// p.kx > 0 (two-term weights): operand X is kx wide, the weight rows
+// [W_hi | W_lo] are 2 kx wide and X is read twice: all high terms are added in
+// the order of k, then all low ones.  (Staging a slice of X once for both terms
+// saves its second read, but adds the low terms beside partial sums of the high
+// ones: where those cancel, the low terms are rounded away.)
 template <class T, int ND1, int ND2, int WM, int WN, int MT, int NT, int EPI, int OCC, bool DB = (OCC >= 2),
-          bool RING = false, int PM = PM_NATIVE, int NB = 2, bool TWO = false, int SL = 1, bool OUT = false>
+          bool RING = false, int PM = PM_NATIVE, int NB = 2, int SL = 1, bool OUT = false>
 __global__ void __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(OCC)))
 k_gemm_nt(const NtArgs<T> p) {
   constexpr int C = 1 + ND1 + ND2;
@@ -277,8 +278,7 @@ k_gemm_nt(const NtArgs<T> p) {
   constexpr int LDSB = RING ? 2 * (XBUF + WBUF) : (2 * STAGE > OUTB ? 2 * STAGE : OUTB);
   static_assert(!RING || (ES == 2 && PM == PM_NATIVE), "direct-to-LDS stages: 16-bit types");
   static_assert(PM == PM_NATIVE || ES == 4, "split products: fp32 storage");
-  static_assert(!OUT || TWO, "fused output layer: two-term ring kernels");
-  static_assert(!TWO || (RING && EPI == EPI_FWD), "two-term stages: ring kernels, forward products");
+  static_assert(!OUT || (RING && EPI == EPI_FWD), "fused output layer: ring kernels, forward products");
   // fp32 mode (fp32 storage, products not split into bf16): tanh in fp64
   constexpr bool X64 = ES == 4 && PM != PM_SPLIT2 && PM != PM_SPLIT3;
   typedef typename Elem<T>::frag frag;
@@ -612,37 +612,32 @@ k_gemm_nt(const NtArgs<T> p) {
     }
     char* const xlds = lds;
     char* const wlds = lds + 2 * XBUF;
-    // stages: k slice sx of X; TWO: weight stage s takes the low (s even) or
-    // the high terms of slice s / 2
-    const int nx = (TWO ? p.kx : p.K) / 64;
-    const int ns = TWO ? 2 * nx : nx;
+    const int ns = p.K / 64;
+    const int nx = p.kx > 0 ? p.kx / 64 : ns;
     auto issue = [&](int s) {
-      const int sx = TWO ? s >> 1 : s;
-      const int64_t wk = TWO ? (int64_t)sx * 128 + ((s & 1) ? 0 : p.kx * (int64_t)ES) : (int64_t)s * 128;
+      const int sx = s >= nx ? s - nx : s;
 #pragma unroll
       for (int i = 0; i < WPW; ++i) {
         if (WG % NW != 0 && wv + i * NW >= WG) break;
 #pragma unroll
         for (int h = 0; h < 2; ++h)
-          __builtin_amdgcn_global_load_lds((const void*)(wsrc[i] + wk + 64 * h + woff[i]),
+          __builtin_amdgcn_global_load_lds((const void*)(wsrc[i] + (int64_t)s * 128 + 64 * h + woff[i]),
                                            (lds_ptr_t)(wlds + (s & 1) * WBUF + h * (WBUF / 2) + (wv + i * NW) * 1024),
                                            16, 0, 0);
       }
-      if (TWO && (s & 1)) return;
-      // (read two stages apart with TWO: the slice's buffer was last read by stage s - 3)
 #pragma unroll
       for (int i = 0; i < XPW; ++i) {
         if (XG % NW != 0 && wv + i * NW >= XG) break;
 #pragma unroll
         for (int h = 0; h < 2; ++h)
           __builtin_amdgcn_global_load_lds((const void*)(xsrc[i] + (int64_t)sx * 128 + 64 * h + xoff[i]),
-                                           (lds_ptr_t)(xlds + (sx & 1) * XBUF + h * (XBUF / 2) + (wv + i * NW) * 1024),
+                                           (lds_ptr_t)(xlds + (s & 1) * XBUF + h * (XBUF / 2) + (wv + i * NW) * 1024),
                                            16, 0, 0);
       }
     };
     frag xf[2][MT][C], wf[2][NT];
     auto read_chunk = [&](int s, int c, int b) {
-      const char* xb = xlds + ((TWO ? s >> 1 : s) & 1) * XBUF + (c >> 1) * (XBUF / 2);
+      const char* xb = xlds + (s & 1) * XBUF + (c >> 1) * (XBUF / 2);
       const char* wb = wlds + (s & 1) * WBUF + (c >> 1) * (WBUF / 2);
 #pragma unroll
       for (int t = 0; t < NT; ++t) wf[b][t] = frag_at(wb, 32 * (wn * NT + t) + (lane & 31), c & 1);
@@ -2611,9 +2606,9 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
           // -> 208 in the reverse)
           if constexpr (C == 1) {
             dim3 grid((unsigned)(((npts + 127) / 128) * ((a.N + 255) / 256)), 1, G);
-            if (a.K >= 512) k_gemm_nt<T, ND1, ND2, 4, 4, 1, 2, EPI, 1, true, false, PM_SPLIT2, 3, false, 2><<<grid, 1024, 0, st>>>(a);
-            else if (EPI == EPI_FWD) k_gemm_nt<T, ND1, ND2, 2, 4, 2, 2, EPI, 1, true, false, PM_SPLIT2, 2, false, 2><<<grid, 512, 0, st>>>(a);
-            else k_gemm_nt<T, ND1, ND2, 4, 4, 1, 2, EPI, 1, true, false, PM_SPLIT2, 2, false, 2><<<grid, 1024, 0, st>>>(a);
+            if (a.K >= 512) k_gemm_nt<T, ND1, ND2, 4, 4, 1, 2, EPI, 1, true, false, PM_SPLIT2, 3, 2><<<grid, 1024, 0, st>>>(a);
+            else if (EPI == EPI_FWD) k_gemm_nt<T, ND1, ND2, 2, 4, 2, 2, EPI, 1, true, false, PM_SPLIT2, 2, 2><<<grid, 512, 0, st>>>(a);
+            else k_gemm_nt<T, ND1, ND2, 4, 4, 1, 2, EPI, 1, true, false, PM_SPLIT2, 2, 2><<<grid, 1024, 0, st>>>(a);
           }
         } else if (a.pm == PM_SPLIT2 && C == 1 && a.N <= 128) {
           // no idle column half at N = 128: 64 points x 128 columns, 2 x 2
@@ -2624,7 +2619,7 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
           if constexpr (C == 1) {
             if (a.N == 128 && npts * G >= 196608 && a.K % 32 == 0) {
               dim3 grid((unsigned)((npts + 127) / 128), 1, G);
-              k_gemm_nt<T, ND1, ND2, 2, 2, 2, 2, EPI, 2, true, false, PM_SPLIT2, 2, false, 2><<<grid, 256, 0, st>>>(a);
+              k_gemm_nt<T, ND1, ND2, 2, 2, 2, 2, EPI, 2, true, false, PM_SPLIT2, 2, 2><<<grid, 256, 0, st>>>(a);
             } else {
               dim3 grid((unsigned)(((npts + 63) / 64) * ((a.N + 127) / 128)), 1, G);
               k_gemm_nt<T, ND1, ND2, 2, 2, 1, 2, EPI, 2, true, false, PM_SPLIT2><<<grid, 256, 0, st>>>(a);
@@ -2704,34 +2699,34 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
     //   reverse  C = 5:  554 / 1425 / 2152 ->  568 / 1446 / 2022 |  480 / 1217 / 1869
     //            C = 3:    - /  862 / 1242 ->  330 /  772 / 1109 |  318 /  881 / 1312
     if constexpr (sizeof(T) == 2 && EPI != EPI_DF && !(EPI == EPI_BWD && C == 1)) {
-      constexpr bool TWO = EPI == EPI_FWD;
-      constexpr int WM = C == 1 ? 4 : 2, WN = C == 1 ? 2 : 4, MT = C <= 3 && TWO ? 2 : 1, NT = C == 1 ? 4 : (C <= 3 || C == 5 ? 2 : 1);
+      constexpr bool FWD = EPI == EPI_FWD;
+      constexpr int WM = C == 1 ? 4 : 2, WN = C == 1 ? 2 : 4, MT = C <= 3 && FWD ? 2 : 1, NT = C == 1 ? 4 : (C <= 3 || C == 5 ? 2 : 1);
       constexpr int BM = 32 * MT * WM, BN = 32 * NT * WN;
       const int64_t blocks = ((npts + BM - 1) / BM) * ((a.N + BN - 1) / BN) * G;
       // (with the output layer fused the large tiles take up to twice as long,
       // five streams at K = 512 1917 us against 1520 on the small one, three
       // 1854 against 1094: the column weights push the accumulators out of the
       // register file)
-      const bool large = !a.y && a.N >= 256 && blocks >= 2 * (int64_t)cu_count() && !(C == 5 && (!TWO || a.N == 256)) &&
-                         !(C == 3 && !TWO && a.N == 256);
-      if constexpr (TWO || C <= 4) {
+      const bool large = !a.y && a.N >= 256 && blocks >= 2 * (int64_t)cu_count() && !(C == 5 && (!FWD || a.N == 256)) &&
+                         !(C == 3 && !FWD && a.N == 256);
+      if constexpr (FWD || C <= 4) {
         if (large) {
           dim3 grid((unsigned)(((npts + BM - 1) / BM) * ((a.N + BN - 1) / BN)), 1, G);
-          k_gemm_nt<T, ND1, ND2, WM, WN, MT, NT, EPI, 1, true, true, PM_NATIVE, 2, TWO><<<grid, 64 * WM * WN, 0, st>>>(a);
+          k_gemm_nt<T, ND1, ND2, WM, WN, MT, NT, EPI, 1, true, true, PM_NATIVE, 2><<<grid, 64 * WM * WN, 0, st>>>(a);
           return hipGetLastError();
         }
       }
       dim3 grid((unsigned)(((npts + 31) / 32) * ((a.N + 127) / 128)), 1, G);
-      if constexpr (TWO && C >= 3) {
+      if constexpr (FWD && C >= 3) {
         if (a.y) {
-          k_gemm_nt<T, ND1, ND2, 1, 4, 1, 1, EPI, (C <= 5 ? 2 : 1), true, true, PM_NATIVE, 2, TWO, 1, true><<<grid, 256, 0, st>>>(a);
+          k_gemm_nt<T, ND1, ND2, 1, 4, 1, 1, EPI, (C <= 5 ? 2 : 1), true, true, PM_NATIVE, 2, 1, true><<<grid, 256, 0, st>>>(a);
           if (a.N > 128)
             k_out_sum<<<dim3((unsigned)((C * npts + 255) / 256), 1, G), 256, 0, st>>>(
                 a.ypart, a.yp_g, a.N / 128, npts, C, a.seg, a.wout, a.wo_g, a.N, a.y, a.y_g);
           return hipGetLastError();
         }
       }
-      k_gemm_nt<T, ND1, ND2, 1, 4, 1, 1, EPI, (C <= 5 ? 2 : 1), true, true, PM_NATIVE, 2, TWO><<<grid, 256, 0, st>>>(a);
+      k_gemm_nt<T, ND1, ND2, 1, 4, 1, 1, EPI, (C <= 5 ? 2 : 1), true, true, PM_NATIVE, 2><<<grid, 256, 0, st>>>(a);
     } else {
       return hipErrorInvalidValue;
     }

@@ -91,3 +91,31 @@ def test_gen_forward_latent_sum(S, n_z, W):
     got = got.cpu().numpy()[0]
     ref = oracle.gen_jets(p[0], shape, 1, z[0], x[0], 1)
     check({f"c{k}": rel(got[k], ref[k]) for k in range(ref.shape[0])}, TOL["fp32"], f"latent S={S} n_z={n_z} W={W}")
+
+
+# two-term weights: all high terms are added in the order of k, then all low
+# ones.  Every row of the second layer holds two weights whose high terms cancel
+# against two of the last slice (of 64 inputs with equal values), and a low term of
+# 2^-12 that alone is left.  2^-12 h beside a sum of 32832 h is below half a
+# unit of the last place of fp32 (2^-9 h): added before the cancellation it is
+# lost, and the field is zero.  After it every sum is exact (32832 h takes 21
+# bits), and the field is that of the 16-bit h, a few 2^-9 from the oracle's.
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("d,order,W", [c for c in CASES if c[0] != 3 or c[1] == 2] + [(1, 0, 1024)])
+def test_two_term_sum_order(d, order, W, dtype):
+    import torch
+    print(f"two-term sum order d={d} order={order} W={W} {dtype}", flush=True)
+    n_z, L, pts = 2, 2, 40
+    shape = (d + n_z, L, W)
+    W1 = np.zeros((W, d + n_z))
+    W1[:, :d] = [0.5, 0.25, 0.75][:d]
+    W2 = np.zeros((W, W))
+    W2[:, 0], W2[:, 1], W2[:, W - 64], W2[:, W - 63] = 32768.0, 64.0 + 2.0 ** -12, -32768.0, -64.0
+    p = np.concatenate([W1.ravel(), np.full(W, 0.25), W2.ravel(), np.zeros(W), np.full(W, 1.0 / W), [0.0]])[None]
+    z = np.ones((1, 1, n_z))
+    x = np.random.default_rng(W).random((1, 1, pts, d))
+    got = pigan.gen_forward(to_dev(p), shape, d, to_dev(z), to_dev(x), order, dtype=dtype)
+    torch.cuda.synchronize()
+    got = got.cpu().numpy()[0]
+    ref = oracle.gen_jets(p[0], shape, d, z[0], x[0], order)
+    check({f"c{k}": rel(got[k], ref[k]) for k in range(ref.shape[0])}, TOL[dtype], f"d={d} order={order} W={W}")
