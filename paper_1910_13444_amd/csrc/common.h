@@ -147,6 +147,30 @@ __device__ __forceinline__ void tanh_pair(float a, float& t, float& s) {
 }
 
 // ---------------------------------------------------------------------------
+// One row of the scalar output layer, w . h, by eight neighbouring lanes (e:
+// the lane's place among them): 16-byte pieces of the row in turn, shuffle
+// reduction; fp32 storage (the sensor rows and the critic) sums in fp64.  All
+// eight lanes get the sum.
+// ---------------------------------------------------------------------------
+template <class T>
+__device__ __forceinline__ typename std::conditional<sizeof(T) == 4, double, float>::type
+out_row_sum(const T* h, const float* w, int W, int e) {
+  constexpr int EPP = 16 / (int)sizeof(T);
+  typedef typename std::conditional<sizeof(T) == 4, double, float>::type Acc;
+  Acc acc = 0;
+  for (int c = e * EPP; c < W; c += 8 * EPP) {
+    const uint4 v = *(const uint4*)(h + c);
+    const T* hv = (const T*)&v;
+#pragma unroll
+    for (int q = 0; q < EPP; ++q) acc += (Acc)w[c + q] * (Acc)Elem<T>::to_f(hv[q]);
+  }
+  acc += __shfl_xor(acc, 1);
+  acc += __shfl_xor(acc, 2);
+  acc += __shfl_xor(acc, 4);
+  return acc;
+}
+
+// ---------------------------------------------------------------------------
 // Launch descriptors (host side builds them, kernels read them by value).
 // Row layout of one network's activations for a chunk of samples:
 //   rows [0, n_sen)                       sensor points (value stream only)

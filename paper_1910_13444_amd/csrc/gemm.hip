@@ -873,6 +873,9 @@ k_gemm_nt(const NtArgs<T> p) {
     // fused output layer: w_out . h over the lane's columns, the activations
     // as stored
     float ys[OUT ? MT : 1][OUT ? C : 1][OUT ? NT : 1];
+    constexpr int HPITCH = 128 * ES + 16;          // of an LDS row of 128 activations
+    static_assert(!OUT || (BN == 128 && BM == 32 && NTH == 256 && C * BM * HPITCH <= LDSB), "fused output layer: 128 columns per block");
+    if (OUT) lds_sync();                           // the stages have been read
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       float bv[16];
@@ -903,7 +906,18 @@ k_gemm_nt(const NtArgs<T> p) {
           for (int k = 0; k < C; ++k) acc[u][k][t][r] = v[k];
           if (MT * C * NT * 16 >= 160 && r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
-        if constexpr (OUT) {
+        if (OUT && p.N == 128) {
+          // whole rows in the block: the activations as stored, into LDS
+#pragma unroll
+          for (int k = 0; k < C; ++k) {
+            FragRaw<T> f;
+            frag_pack<T>(f, acc[u][k][t]);
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+              *(u32x4*)(lds + (k * BM + 32 * (MT * wm + u) + (lane & 15) + 16 * j) * HPITCH +
+                        (32 * (wn * NT + t) + frag_col<T>(lane, 0)) * ES) = f.w[0][j];
+          }
+        } else if constexpr (OUT) {
           // (N is a multiple of 128: whole fragments)
           const float* wp = p.wout + g * p.wo_g + (fcol(t) < p.N ? fcol(t) : 0) + 4 * hh;
           float wo[16];
@@ -933,11 +947,26 @@ k_gemm_nt(const NtArgs<T> p) {
       }
     }
     if constexpr (OUT) {
+      if (p.N == 128) {
+        // as k_out_fwd sums a row: the same bits
+        lds_sync();
+        const float* w = p.wout + g * p.wo_g;
+        const int64_t pt = m0 + (tid >> 3);
+        float v[C];
+#pragma unroll
+        for (int k = 0; k < C; ++k)
+          v[k] = out_row_sum<T>((const T*)(lds + (k * BM + (tid >> 3)) * HPITCH), w, 128, tid & 7);
+        if ((tid & 7) == 0 && pt < npts) {
+#pragma unroll
+          for (int k = 0; k < C; ++k)
+            p.y[g * p.y_g + p.seg.row0 + k * p.seg.plane + pt] = v[k] + (k == 0 ? w[128] : 0.0f);
+        }
+        return;
+      }
       // the lane halves, then the four fragments of each 128 columns in column
       // order, whatever waves and tiles hold them: the result does not depend
       // on the tile shape.  k_out_sum adds the groups of 128.
       float* red = (float*)lds;                    // [BN / 32][C][BM]
-      lds_sync();                                  // the stages have been read
 #pragma unroll
       for (int u = 0; u < MT; ++u)
 #pragma unroll
@@ -948,15 +977,13 @@ k_gemm_nt(const NtArgs<T> p) {
             if (hh == 0) red[((wn * NT + t) * C + k) * BM + mloc(u)] = v;
           }
       lds_sync();
-      const int groups = p.N / 128;
       for (int i = tid; i < (BN / 128) * C * BM; i += NTH) {
         const int gr = i / (C * BM), k = i / BM % C;
         const int64_t pt = m0 + i % BM;
         const float* f = red + (int64_t)gr * 4 * C * BM + i % (C * BM);
         const float v = ((f[0] + f[C * BM]) + f[2 * C * BM]) + f[3 * C * BM];
-        if (pt >= npts || n0 / 128 + gr >= groups) continue;
-        if (groups == 1) p.y[g * p.y_g + p.seg.row0 + k * p.seg.plane + pt] = k == 0 ? v + p.wout[g * p.wo_g + p.N] : v;
-        else p.ypart[g * p.yp_g + (int64_t)(n0 / 128 + gr) * C * npts + k * npts + pt] = v;
+        if (pt >= npts || n0 + 128 * gr >= p.N) continue;
+        p.ypart[g * p.yp_g + (int64_t)(n0 / 128 + gr) * C * npts + k * npts + pt] = v;
       }
     }
     return;

@@ -171,32 +171,19 @@ k_first_fwd(FirstArgs<T> p) {
 
 // ---------------------------------------------------------------------------
 // scalar output layer: y[row] = w_out . H[row] (+ b_out on value rows)
-// eight lanes per row, 16-byte loads, shuffle reduction; fp32 storage (the
-// sensor rows and the critic) sums in fp64
+// (out_row_sum: eight lanes per row)
 // ---------------------------------------------------------------------------
 template <class T>
 __global__ void __launch_bounds__(256)
 k_out_fwd(const T* __restrict__ H, int64_t h_g, int64_t ldh, int64_t R, int64_t n_value, int W,
           const float* __restrict__ wout, int64_t w_g, float* __restrict__ y, int64_t y_g) {
-  constexpr int EPP = 16 / (int)sizeof(T);
   const int g = blockIdx.z;
   const int team = threadIdx.x >> 3, e = threadIdx.x & 7;
   const int64_t row = (int64_t)blockIdx.x * 32 + team;
-  typedef typename std::conditional<sizeof(T) == 4, double, float>::type Acc;
   const float* w = wout + g * w_g;
-  Acc acc = 0;
-  if (row < R) {
-    const T* hr = H + g * h_g + row * ldh;
-    for (int c = e * EPP; c < W; c += 8 * EPP) {
-      uint4 v = *(const uint4*)(hr + c);
-      const T* hv = (const T*)&v;
-#pragma unroll
-      for (int q = 0; q < EPP; ++q) acc += (Acc)w[c + q] * (Acc)Elem<T>::to_f(hv[q]);
-    }
-  }
-  acc += __shfl_xor(acc, 1);
-  acc += __shfl_xor(acc, 2);
-  acc += __shfl_xor(acc, 4);
+  // (rows past the end sum the last one)
+  const auto acc = out_row_sum<T>(H + g * h_g + (row < R ? row : R - 1) * ldh, w, W, e);
+  typedef decltype(out_row_sum<T>(H, w, W, e)) Acc;
   if (row < R && e == 0) y[g * y_g + row] = (float)(acc + (row < n_value ? (Acc)w[W] : (Acc)0));
 }
 

@@ -119,3 +119,33 @@ def test_two_term_sum_order(d, order, W, dtype):
     got = got.cpu().numpy()[0]
     ref = oracle.gen_jets(p[0], shape, d, z[0], x[0], order)
     check({f"c{k}": rel(got[k], ref[k]) for k in range(ref.shape[0])}, TOL[dtype], f"d={d} order={order} W={W}")
+
+
+# output layer of a 16-bit row: eight lanes sum pieces of eight columns in turn
+# (fp32), then meet pairwise, whether a pass of its own reads the row or, for 128
+# columns, the block that formed it.  Saturated units (+-1) make every product
+# exact, so the sum follows from its order alone: the same bits.
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("d,order,W,pts", [(3, 2, 128, 1), (3, 2, 128, 77), (2, 0, 256, 77), (1, 1, 512, 33)])
+def test_output_layer_sum_order(d, order, W, pts, dtype):
+    import torch
+    print(f"output layer sum order d={d} order={order} W={W} points={pts} {dtype}", flush=True)
+    rng = np.random.default_rng(W + pts)
+    n_z, L = 2, 2
+    shape = (d + n_z, L, W)
+    h = rng.choice([-1.0, 1.0], W).astype(np.float32)
+    w_out, b_out = rng.standard_normal(W).astype(np.float32), np.float32(0.3)
+    p = np.concatenate([np.zeros(W * (d + n_z) + W + W * W), 40.0 * h, w_out, [b_out]])[None]
+    got = pigan.gen_forward(to_dev(p), shape, d, to_dev(np.ones((1, 1, n_z))), to_dev(rng.random((1, 1, pts, d))), order,
+                            dtype=dtype)
+    torch.cuda.synchronize()
+    lane = np.zeros(8, np.float32)
+    for c in range(0, W, 64):
+        for e in range(8):
+            for q in range(8):
+                lane[e] += w_out[c + 8 * e + q] * h[c + 8 * e + q]
+    for s in (1, 2, 4):
+        lane = lane + lane[np.arange(8) ^ s]
+    got = got.cpu().numpy()[0].reshape(-1, pts)
+    assert (got[0] == lane[0] + b_out).all(), (got[0][0], lane[0] + b_out)
+    assert (got[1:] == 0).all()
