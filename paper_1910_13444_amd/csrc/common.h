@@ -58,43 +58,26 @@ template <> struct Elem<f16> {
 
 // ---------------------------------------------------------------------------
 // Split products for fp32 storage.  A fragment of 8 fp32 values is cut into
-// bf16 pieces x = x0 + x1 (+ x2) by repeated round-to-nearest: each residual
-// is exact in fp32, so two pieces carry about 16 significand bits and three
-// pieces carry all 24 of an fp32 value.  Products of bf16 pieces are exact in
-// the matrix core's fp32 accumulator.
+// two bf16 pieces x = x0 + x1 by repeated round-to-nearest: the residual is
+// exact in fp32, so the pieces carry about 16 significand bits.  Products of
+// bf16 pieces are exact in the matrix core's fp32 accumulator.
 //   PM_SPLIT2: x0 y0 + x0 y1 + x1 y0  (about 2^-16 relative; x1 y1 dropped)
-//   PM_SPLIT3: all pieces with i + j <= 2 (the terms dropped are below 2^-24
-//              relative), accumulated per operand stage and then in fp64
-//              by the kernels, so that long contractions do not round at
-//              fp32 precision at every step.
-// ---------------------------------------------------------------------------
 //   PM_F64:    the fp32 operands go through the fp64 matrix core (exact
 //              products, fp64 accumulation), rounded once at the end.
-enum ProdMode { PM_NATIVE = 0, PM_SPLIT2 = 2, PM_SPLIT3 = 3, PM_F64 = 4 };
+// ---------------------------------------------------------------------------
+enum ProdMode { PM_NATIVE = 0, PM_SPLIT2 = 2, PM_F64 = 4 };
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-template <int NP>
-__device__ __forceinline__ void split_frag(const f32x8& x, bf16x8 (&p)[NP]) {
+__device__ __forceinline__ void split_frag(const f32x8& x, bf16x8 (&p)[2]) {
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
-    float r = x[q];
-#pragma unroll
-    for (int i = 0; i < NP; ++i) {
-      const bf16 h = (bf16)r;
-      p[i][q] = h;
-      r -= (float)h;
-    }
+    p[0][q] = (bf16)x[q];
+    p[1][q] = (bf16)(x[q] - (float)p[0][q]);
   }
 }
 
 // acc += b . a over one 16-wide chunk from split operands (smallest terms first)
-template <int NP>
-__device__ __forceinline__ void mma_split(f32x16& acc, const bf16x8 (&b)[NP], const bf16x8 (&a)[NP]) {
-  if constexpr (NP == 3) {
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[2], a[0], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[1], a[1], acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[0], a[2], acc, 0, 0, 0);
-  }
+__device__ __forceinline__ void mma_split(f32x16& acc, const bf16x8 (&b)[2], const bf16x8 (&a)[2]) {
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[1], a[0], acc, 0, 0, 0);
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[0], a[1], acc, 0, 0, 0);
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[0], a[0], acc, 0, 0, 0);
@@ -246,7 +229,7 @@ void prof_end(hipStream_t st);
 template <class T>
 hipError_t launch_gemm_nt(int epi, int nd1, int nd2, const NtArgs<T>& a, int G, hipStream_t st);
 
-// pm: ProdMode for fp32 storage; PM_SPLIT3 and PM_F64 write their split
+// pm: ProdMode for fp32 storage; PM_F64 writes its split
 // partials in fp64 to partial64 instead of partial
 template <class T>
 hipError_t launch_gemm_dw(const T* dA, int64_t a_g, int64_t lda, const T* H, int64_t h_g, int64_t ldh,

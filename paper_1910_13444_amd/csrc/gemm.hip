@@ -251,7 +251,7 @@ typedef __attribute__((address_space(3))) void* lds_ptr_t;
 // 16 x 256-wide, 512-wide and 1024-wide generators 63.9 -> 62.4, 36.2 -> 35.8
 // and 164.1 -> 163.5 ms).
 // PM (fp32 storage only): products from bf16 pieces of the fp32 operands
-// (ProdMode); PM_SPLIT3 folds the accumulators into fp64 after every stage.
+// (ProdMode).
 // p.kx > 0 (two-term weights): operand X is kx wide, the weight rows
 // [W_hi | W_lo] are 2 kx wide and X is read twice: all high terms are added in
 // the order of k, then all low ones.  (Staging a slice of X once for both terms
@@ -280,7 +280,7 @@ k_gemm_nt(const NtArgs<T> p) {
   static_assert(PM == PM_NATIVE || ES == 4, "split products: fp32 storage");
   static_assert(!OUT || (RING && EPI == EPI_FWD), "fused output layer: ring kernels, forward products");
   // fp32 mode (fp32 storage, products not split into bf16): tanh in fp64
-  constexpr bool X64 = ES == 4 && PM != PM_SPLIT2 && PM != PM_SPLIT3;
+  constexpr bool X64 = ES == 4 && PM != PM_SPLIT2;
   typedef typename Elem<T>::frag frag;
   __shared__ __attribute__((aligned(16))) char lds[LDSB];
 
@@ -430,7 +430,6 @@ k_gemm_nt(const NtArgs<T> p) {
   // segments in fp32); every fragment row base is a multiple of 32, so the
   // segment swizzle of the lane's row is (lane >> 2) & 3
   const int gsw = (lane >> 2) & 3;
-  bool odd = false;   // PM_SPLIT3: operand X negated in this stage
   auto frag_at = [&](const char* base, int row, int c) {
     if constexpr (ES == 2) {
       const int seg = 2 * c + (lane >> 5);
@@ -462,30 +461,7 @@ k_gemm_nt(const NtArgs<T> p) {
 #pragma unroll
           for (int c = 0; c < 2; ++c) ap[c] = piece_at(base, k * BM + 32 * (MT * wm + u) + (lane & 31), c);
 #pragma unroll
-          for (int t = 0; t < NT; ++t) mma_split<2>(acc[u][k][t], bp[t], ap);
-        }
-      return;
-    }
-    if constexpr (PM != PM_NATIVE) {
-      // PM_SPLIT3: fp32 fragments (one chunk per stage), each cut into bf16
-      // pieces as it is read.  PM_SPLIT3 negates operand X on every other stage (the fold subtracts
-      // those stages): the matrix core's sums carry a small bias of one sign
-      // whatever the sign of the result, which then cancels in the fp64 sum
-      // instead of adding up over the stages.
-      constexpr int NP = PM == PM_SPLIT3 ? 3 : 2;
-      bf16x8 bp[NT][NP];
-#pragma unroll
-      for (int t = 0; t < NT; ++t) split_frag<NP>(frag_at(base, C * BM + 32 * (wn * NT + t) + (lane & 31), 0), bp[t]);
-#pragma unroll
-      for (int u = 0; u < MT; ++u)
-#pragma unroll
-        for (int k = 0; k < C; ++k) {
-          bf16x8 ap[NP];
-          f32x8 xf = frag_at(base, k * BM + 32 * (MT * wm + u) + (lane & 31), 0);
-          if (PM == PM_SPLIT3 && odd) xf = -xf;
-          split_frag<NP>(xf, ap);
-#pragma unroll
-          for (int t = 0; t < NT; ++t) mma_split<NP>(acc[u][k][t], bp[t], ap);
+          for (int t = 0; t < NT; ++t) mma_split(acc[u][k][t], bp[t], ap);
         }
       return;
     }
@@ -545,37 +521,6 @@ k_gemm_nt(const NtArgs<T> p) {
         }
     }
   };
-  // PM_SPLIT3: the stage's fp32 sums are added into (odd stages: subtracted
-  // from) fp64 accumulators
-  constexpr int A64 = PM == PM_SPLIT3 ? 1 : 0;
-  double acc64[A64 ? MT : 1][A64 ? C : 1][A64 ? NT : 1][A64 ? 16 : 1];
-  if constexpr (A64) {
-#pragma unroll
-    for (int u = 0; u < MT; ++u)
-#pragma unroll
-      for (int k = 0; k < C; ++k)
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc64[u][k][t][r] = 0.0;
-  }
-  auto fold = [&]() {
-    if constexpr (A64) {
-#pragma unroll
-      for (int u = 0; u < MT; ++u)
-#pragma unroll
-        for (int k = 0; k < C; ++k)
-#pragma unroll
-          for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              acc64[u][k][t][r] += odd ? -(double)acc[u][k][t][r] : (double)acc[u][k][t][r];
-              acc[u][k][t][r] = 0.0f;
-            }
-      odd = !odd;
-    }
-  };
-
   if constexpr (RING) {
     // One DMA instruction of a wave fills 1 KB of LDS, lane l at byte 16 l:
     // 16 rows of a slice (row 16 g + l / 4, physical segment l % 4, holding
@@ -717,7 +662,6 @@ k_gemm_nt(const NtArgs<T> p) {
         const int kt = k0 + u;
         if (kt >= nk) break;
         if constexpr (PM == PM_F64) compute64(kt & 1); else compute(kt & 1);
-        fold();
         __builtin_amdgcn_sched_barrier(0);
         if (kt + 1 < nk) lstore(bufs[(u + 1) % NB], (kt + 1) & 1);
         gload(bufs[(u + 1) % NB], kt + 1 + NB < last ? kt + 1 + NB : last);
@@ -738,14 +682,12 @@ k_gemm_nt(const NtArgs<T> p) {
     for (int kt = 0; kt < nk; kt += 2) {
       gload(b0, kt + 2 < nk ? kt + 2 : nk - 1);
       if constexpr (PM == PM_F64) compute64(0); else compute(0);
-      fold();
       __builtin_amdgcn_sched_barrier(0);
       if (kt + 1 < nk) lstore(b1, 1);
       lds_sync();
       if (kt + 1 >= nk) break;
       gload(b1, kt + 3 < nk ? kt + 3 : nk - 1);
       if constexpr (PM == PM_F64) compute64(1); else compute(1);
-      fold();
       __builtin_amdgcn_sched_barrier(0);
       if (kt + 2 < nk) lstore(b0, 0);
       lds_sync();
@@ -760,21 +702,10 @@ k_gemm_nt(const NtArgs<T> p) {
     for (int kt = 0; kt < nk; ++kt) {
       gload(b0, kt + 1 < nk ? kt + 1 : nk - 1);
       if constexpr (PM == PM_F64) compute64(kt & 1); else compute(kt & 1);
-      fold();
       __builtin_amdgcn_sched_barrier(0);
       if (kt + 1 < nk) lstore(b0, (kt + 1) & 1);
       lds_sync();
     }
-  }
-  if constexpr (A64) {
-#pragma unroll
-    for (int u = 0; u < MT; ++u)
-#pragma unroll
-      for (int k = 0; k < C; ++k)
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[u][k][t][r] = (float)acc64[u][k][t][r];
   }
   if constexpr (PM == PM_F64) {
     // each stream through LDS, [point][column] floats (pitch 65), into the
@@ -1300,8 +1231,8 @@ __global__ void __launch_bounds__(64) k_gemm_short_x2(const NtArgs<float> p) {
         const u32x8 w = {xb[b][i][k][0].x, xb[b][i][k][0].y, xb[b][i][k][0].z, xb[b][i][k][0].w,
                          xb[b][i][k][1].x, xb[b][i][k][1].y, xb[b][i][k][1].z, xb[b][i][k][1].w};
         bf16x8 ax[2];
-        split_frag<2>(__builtin_bit_cast(f32x8, w), ax);
-        mma_split<2>(acc[k], bw, ax);
+        split_frag(__builtin_bit_cast(f32x8, w), ax);
+        mma_split(acc[k], bw, ax);
       }
     }
   };
@@ -1820,9 +1751,8 @@ __device__ __forceinline__ int dw_col(int c) {
   return (c >> 5) * 2624 + (c & 31) * 80 + ((c & 16) ? 64 : 0);
 }
 
-// PM (fp32 storage): products from bf16 pieces (ProdMode); with PM_SPLIT3
-// the stage sums are folded into fp64 and the split partials are written in
-// fp64 to partial64 (partial is unused).
+// PM (fp32 storage): how the products are formed (ProdMode); with PM_F64 the
+// split partials are written in fp64 to partial64 (partial is unused).
 template <class T, int WM, int WN, int NT, int OCC, int NB, int PM = PM_NATIVE>
 __global__ void __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(OCC)))
 k_gemm_dw(const T* __restrict__ dA, int64_t a_g, int64_t lda, const T* __restrict__ H, int64_t h_g,
@@ -1883,16 +1813,6 @@ k_gemm_dw(const T* __restrict__ dA, int64_t a_g, int64_t lda, const T* __restric
     for (int b = 0; b < NT; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.0f;
-  constexpr int A64 = PM == PM_SPLIT3 ? 1 : 0;
-  double acc64[A64 ? NT : 1][A64 ? NT : 1][A64 ? 16 : 1];
-  if constexpr (A64) {
-#pragma unroll
-    for (int a = 0; a < NT; ++a)
-#pragma unroll
-      for (int b = 0; b < NT; ++b)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc64[a][b][r] = 0.0;
-  }
   // PM_F64: a wave's 32 x 32 outputs as 2 x 2 blocks of the 16 x 16 fp64
   // product (lane l: rows (l >> 4) + 4 r, column l & 15 of a block)
   static_assert(PM != PM_F64 || NT == 1, "fp64 products: one fragment per wave");
@@ -1902,7 +1822,6 @@ k_gemm_dw(const T* __restrict__ dA, int64_t a_g, int64_t lda, const T* __restric
 #pragma unroll
     for (int b = 0; b < 2; ++b) accd[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
   double dbacc = 0.0;
-  bool odd = false;   // PM_SPLIT3: dA negated in this stage
 
   // piece q of an operand: row piece q % NRP, column group q / NRP
   auto gload = [&](uint4 (*buf)[RPP], int64_t k0) {
@@ -1998,7 +1917,7 @@ k_gemm_dw(const T* __restrict__ dA, int64_t a_g, int64_t lda, const T* __restric
 #pragma unroll
       for (int a = 0; a < NT; ++a)
 #pragma unroll
-        for (int b = 0; b < NT; ++b) mma_split<2>(acc[a][b], ap[a], bp[b]);
+        for (int b = 0; b < NT; ++b) mma_split(acc[a][b], ap[a], bp[b]);
     }
 #pragma unroll
     for (int c = 0; c < (PM == PM_F64 || SPL ? 0 : NCH); ++c) {
@@ -2009,38 +1928,10 @@ k_gemm_dw(const T* __restrict__ dA, int64_t a_g, int64_t lda, const T* __restric
         af[t] = *(const frag*)(base + dw_col(32 * (wm * NT + t) + (lane & 31)) + koff);
         bf[t] = *(const frag*)(base + REGA + dw_col(32 * (wn * NT + t) + (lane & 31)) + koff);
       }
-      if constexpr (PM != PM_NATIVE) {
-        // PM_SPLIT3 negates dA on every other stage and subtracts those
-        // stages in the fp64 fold (the matrix core's one-signed bias cancels)
-        constexpr int NP = PM == PM_SPLIT3 ? 3 : 2;
-        bf16x8 ap[NT][NP], bp[NT][NP];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          split_frag<NP>(PM == PM_SPLIT3 && odd ? -af[t] : af[t], ap[t]);
-          split_frag<NP>(bf[t], bp[t]);
-        }
-#pragma unroll
-        for (int a = 0; a < NT; ++a)
-#pragma unroll
-          for (int b = 0; b < NT; ++b) mma_split<NP>(acc[a][b], ap[a], bp[b]);
-      } else {
-#pragma unroll
-        for (int a = 0; a < NT; ++a)
-#pragma unroll
-          for (int b = 0; b < NT; ++b) Elem<T>::mma(acc[a][b], af[a], bf[b]);
-      }
-    }
-    if constexpr (PM == PM_SPLIT3) {
 #pragma unroll
       for (int a = 0; a < NT; ++a)
 #pragma unroll
-        for (int b = 0; b < NT; ++b)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            acc64[a][b][r] += odd ? -(double)acc[a][b][r] : (double)acc[a][b][r];
-            acc[a][b][r] = 0.0f;
-          }
-      odd = !odd;
+        for (int b = 0; b < NT; ++b) Elem<T>::mma(acc[a][b], af[a], bf[b]);
     }
     // bias cotangent: value rows of this slice, one column per thread
     // (the 64-byte column line is read as 16 independent words)
@@ -2139,8 +2030,7 @@ k_gemm_dw(const T* __restrict__ dA, int64_t a_g, int64_t lda, const T* __restric
       for (int r = 0; r < 16; ++r) {
         const int n = n0 + 32 * (wm * NT + a) + 8 * (r >> 2) + 4 * hh + (r & 3);
         if (n >= N) continue;
-        if constexpr (A64) partial64[obase + (int64_t)n * J + j] = acc64[a][b][r];
-        else partial[obase + (int64_t)n * J + j] = acc[a][b][r];
+        partial[obase + (int64_t)n * J + j] = acc[a][b][r];
       }
     }
   }
@@ -2585,7 +2475,7 @@ int cu_count() {
 template <class T, int C, int EPI>
 bool ring_ok(const NtArgs<T>& a) {
   const int kx = a.kx > 0 ? a.kx : a.K;
-  return sizeof(T) == 2 && EPI != EPI_DF && !(EPI == EPI_BWD && C == 1) && (EPI == EPI_FWD) == (a.kx > 0) && a.N >= 128 &&
+  return sizeof(T) == 2 && (EPI == EPI_FWD) == (a.kx > 0) && a.N >= 128 &&
          kx >= 128 && kx % 64 == 0 && a.ldx < (1 << 22) && a.ldw < (1 << 22);
 }
 
@@ -2596,7 +2486,8 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
   const int64_t npts = a.seg.n_points;
   if (npts <= 0) return hipSuccess;
   if (EPI == EPI_FWD && !a.bias) return hipErrorInvalidValue;
-  if ((a.pm != PM_NATIVE && sizeof(T) != 4) || (a.kx > 0 && (sizeof(T) != 2 || a.K != 2 * a.kx)))
+  if ((a.pm != PM_NATIVE && a.pm != PM_SPLIT2 && a.pm != PM_F64) || (a.pm != PM_NATIVE && sizeof(T) != 4) ||
+       (a.kx > 0 && (sizeof(T) != 2 || a.K != 2 * a.kx)))
     return hipErrorInvalidValue;
   if constexpr (sizeof(T) == 4) {
     // split products (the critic and the generators' sensor rows): one or two
@@ -2613,7 +2504,7 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
         // (512) 14.2 -> 10.5, 1024 blocks 15.2 -> 15.5
         const int64_t sblocks = ((npts + 31) / 32) * (a.N / 32) * G;
         const int64_t limit = (a.pm == PM_F64 ? 3 : a.K >= 256 ? 4 : 2) * (int64_t)cu_count();
-        if (a.pm != PM_SPLIT3 && a.N % 32 == 0 && a.K % 16 == 0 && sblocks <= limit) {
+        if (a.N % 32 == 0 && a.K % 16 == 0 && sblocks <= limit) {
           dim3 grid((unsigned)(((npts + 31) / 32) * (a.N / 32)), 1, G);
           if (a.pm == PM_SPLIT2) k_gemm_short_x2<ND1, EPI><<<grid, 64, 0, st>>>(a);
           else if (a.K >= 1024) k_gemm_short<ND1, EPI, 8><<<grid, 512, 0, st>>>(a);   // (eight waves share the contraction)
@@ -2622,8 +2513,7 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
         }
         if (a.N <= 32 && a.pm != PM_F64) {
           dim3 grid((unsigned)(((npts + 127) / 128) * ((a.N + 31) / 32)), 1, G);
-          if (a.pm == PM_SPLIT2) k_gemm_nt<T, ND1, ND2, 4, 1, 1, 1, EPI, 2, true, false, PM_SPLIT2><<<grid, 256, 0, st>>>(a);
-          else k_gemm_nt<T, ND1, ND2, 4, 1, 1, 1, EPI, 2, true, false, PM_SPLIT3><<<grid, 256, 0, st>>>(a);
+          k_gemm_nt<T, ND1, ND2, 4, 1, 1, 1, EPI, 2, true, false, PM_SPLIT2><<<grid, 256, 0, st>>>(a);
         } else if (a.pm == PM_SPLIT2 && C == 1 && a.N >= 256 && npts * G >= 16384 && a.K % 32 == 0) {
           // sensor rows: 128 points x 256 columns, stages of two k slices (a
           // whole 128-byte line of every row at once).  us per forward launch
@@ -2657,14 +2547,10 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
           constexpr int BN = 64 * NTM;
           dim3 grid((unsigned)(((npts + 63) / 64) * ((a.N + BN - 1) / BN)), 1, G);
           k_gemm_nt<T, ND1, ND2, 2, 2, 1, NTM, EPI, 2, true, false, PM_SPLIT2><<<grid, 256, 0, st>>>(a);
-        } else if (a.pm == PM_F64) {
+        } else {
           // fp64 products: 64 x 64 tiles
           dim3 grid((unsigned)(((npts + 63) / 64) * ((a.N + 63) / 64)), 1, G);
           k_gemm_nt<T, ND1, ND2, 2, 2, 1, 1, EPI, 2, true, false, PM_F64><<<grid, 256, 0, st>>>(a);
-        } else {
-          // fp64 stage sums: 64 x 64 tiles
-          dim3 grid((unsigned)(((npts + 63) / 64) * ((a.N + 63) / 64)), 1, G);
-          k_gemm_nt<T, ND1, ND2, 2, 2, 1, 1, EPI, 2, true, false, PM_SPLIT3><<<grid, 256, 0, st>>>(a);
         }
         return hipGetLastError();
       } else {
@@ -2672,7 +2558,7 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
       }
     }
   }
-  if constexpr (sizeof(T) == 2 && C <= 5 && EPI != EPI_DF) {
+  if constexpr (sizeof(T) == 2 && C <= 5) {
     const bool skip = a.skip || a.skip_g || a.out_gh;
     const bool two = a.kx > 0;   // two-term weight rows: the operand is kx wide
     if (nt_resident_ok((int)sizeof(T), C, two ? a.kx : a.K, a.N, npts, a.ldx, a.ldo) &&
@@ -2725,7 +2611,7 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
     //            C = 1:  719 / 2080 / 3251 ->  545 / 1492 / 2317 (4 x the points)
     //   reverse  C = 5:  554 / 1425 / 2152 ->  568 / 1446 / 2022 |  480 / 1217 / 1869
     //            C = 3:    - /  862 / 1242 ->  330 /  772 / 1109 |  318 /  881 / 1312
-    if constexpr (sizeof(T) == 2 && EPI != EPI_DF && !(EPI == EPI_BWD && C == 1)) {
+    if constexpr (sizeof(T) == 2) {
       constexpr bool FWD = EPI == EPI_FWD;
       constexpr int WM = C == 1 ? 4 : 2, WN = C == 1 ? 2 : 4, MT = C <= 3 && FWD ? 2 : 1, NT = C == 1 ? 4 : (C <= 3 || C == 5 ? 2 : 1);
       constexpr int BM = 32 * MT * WM, BN = 32 * NT * WN;
@@ -2768,8 +2654,13 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
 template <class T, int EPI>
 hipError_t nt_dispatch_streams(int nd1, int nd2, const NtArgs<T>& a, int G, hipStream_t st) {
   const int key = nd1 * 10 + nd2;
+  // (one stream backward is the sensor rows' and the critic's, whose storage is fp32)
+  if constexpr (sizeof(T) == 2 && EPI == EPI_BWD) {
+    if (key == 0) return hipErrorInvalidValue;
+  } else {
+    if (key == 0) return nt_dispatch_tile<T, 0, 0, EPI>(a, G, st);
+  }
   switch (key) {
-    case 0: return nt_dispatch_tile<T, 0, 0, EPI>(a, G, st);
     case 10: return nt_dispatch_tile<T, 1, 0, EPI>(a, G, st);
     case 20: return nt_dispatch_tile<T, 2, 0, EPI>(a, G, st);
     case 30: return nt_dispatch_tile<T, 3, 0, EPI>(a, G, st);
@@ -2786,8 +2677,10 @@ template <class T>
 hipError_t launch_gemm_nt(int epi, int nd1, int nd2, const NtArgs<T>& a, int G, hipStream_t st) {
   if (epi == EPI_FWD) return nt_dispatch_streams<T, EPI_FWD>(nd1, nd2, a, G, st);
   if (epi == EPI_BWD) return nt_dispatch_streams<T, EPI_BWD>(nd1, nd2, a, G, st);
-  if (nd1 != 0 || nd2 != 0) return hipErrorInvalidValue;
-  return nt_dispatch_tile<T, 0, 0, EPI_DF>(a, G, st);
+  if constexpr (sizeof(T) == 4) {   // (the critic's storage)
+    if (nd1 == 0 && nd2 == 0) return nt_dispatch_tile<T, 0, 0, EPI_DF>(a, G, st);
+  }
+  return hipErrorInvalidValue;
 }
 
 void dw_split_plan(int64_t R, int N, int J, int elem_bytes, int G, int* n_split, int64_t* rows_per_split) {
@@ -2820,8 +2713,9 @@ hipError_t launch_gemm_dw(const T* dA, int64_t a_g, int64_t lda, const T* H, int
                           int64_t R, int64_t n_value, int N, int J, float* partial, double* pdb,
                           int n_split, int64_t rows_per_split, int G, hipStream_t st, int pm, double* partial64) {
   if (R <= 0) return hipSuccess;
-  if (pm != PM_NATIVE && sizeof(T) != 4) return hipErrorInvalidValue;
-  if ((pm == PM_SPLIT3 || pm == PM_F64) && !partial64) return hipErrorInvalidValue;
+  if ((pm != PM_NATIVE && pm != PM_SPLIT2 && pm != PM_F64) || (pm != PM_NATIVE && sizeof(T) != 4) ||
+      (pm == PM_F64 && !partial64))
+    return hipErrorInvalidValue;
   if constexpr (sizeof(T) == 4) {
     if (pm == PM_F64) {
       dim3 grid((unsigned)(((N + 63) / 64) * ((J + 63) / 64)) * n_split, 1, G);
@@ -2833,16 +2727,11 @@ hipError_t launch_gemm_dw(const T* dA, int64_t a_g, int64_t lda, const T* H, int
 #define PIGAN_DW_PM(WM_, WN_, NT_, NTH_, BT_)                                                                     \
   do {                                                                                                           \
     dim3 grid((unsigned)(((N + BT_ - 1) / BT_) * ((J + BT_ - 1) / BT_)) * n_split, 1, G);                         \
-    if (pm == PM_SPLIT2)                                                                                         \
-      k_gemm_dw<T, WM_, WN_, NT_, 2, 4, PM_SPLIT2><<<grid, NTH_, 0, st>>>(dA, a_g, lda, H, h_g, ldh, R, n_value, N, \
-                                                                       J, partial, pdb, n_split, rows_per_split,   \
-                                                                       partial64);                                 \
-    else                                                                                                         \
-      k_gemm_dw<T, WM_, WN_, NT_, 2, 2, PM_SPLIT3><<<grid, NTH_, 0, st>>>(dA, a_g, lda, H, h_g, ldh, R, n_value, N, \
-                                                                       J, partial, pdb, n_split, rows_per_split,   \
-                                                                       partial64);                                 \
+    k_gemm_dw<T, WM_, WN_, NT_, 2, 4, PM_SPLIT2><<<grid, NTH_, 0, st>>>(dA, a_g, lda, H, h_g, ldh, R, n_value, N, J, \
+                                                                       partial, pdb, n_split, rows_per_split,     \
+                                                                       partial64);                                \
   } while (0)
-      if (N >= 256 && J >= 256 && pm == PM_SPLIT2) {
+      if (N >= 256 && J >= 256) {
         // 256 x 256, 16 waves of 64 x 64 (the fastest measured at 1024 x 1024)
         dim3 grid((unsigned)(((N + 255) / 256) * ((J + 255) / 256)) * n_split, 1, G);
         k_gemm_dw<T, 4, 4, 2, 1, 2, PM_SPLIT2><<<grid, 1024, 0, st>>>(dA, a_g, lda, H, h_g, ldh, R, n_value, N, J,

@@ -187,8 +187,8 @@ static int64_t ob_ppb(int64_t n_points, int W) {
 // per operand (about 16 significand bits each, three products) keep those
 // gradients well inside the accuracy of the 16-bit collocation rows.
 template <class T> constexpr int adv_pm() { return sizeof(T) == 2 ? PM_SPLIT2 : PM_F64; }
-// split-K partials of these product modes are fp64
-static bool pm_wide(int pm) { return pm == PM_SPLIT3 || pm == PM_F64; }
+// split-K partials of the fp64 products are fp64
+static bool pm_wide(int pm) { return pm == PM_F64; }
 // 16-bit storage: the collocation forward products take two-term weights
 // [W_hi | W_lo], so the generated fields and their derivatives see the fp32
 // weights to about 16 significand bits (the residual at the initial weights is
@@ -196,7 +196,7 @@ static bool pm_wide(int pm) { return pm == PM_SPLIT3 || pm == PM_F64; }
 template <class T> constexpr bool two_term() { return sizeof(T) == 2; }
 
 static const char* pm_tag(int pm) {
-  return pm == PM_SPLIT2 ? "_x2" : (pm == PM_SPLIT3 ? "_x3" : (pm == PM_F64 ? "_f64" : ""));
+  return pm == PM_SPLIT2 ? "_x2" : (pm == PM_F64 ? "_f64" : "");
 }
 
 // ---------------------------------------------------------------------------
@@ -341,7 +341,7 @@ static void plan_disc(Carver& cv, DiscBuf& D, const pigan_mlp& disc, int64_t Bma
   D.ob = cv.take((size_t)D.ob_slots * (WD + 1) * 8 * GD);
 }
 
-// split-K partials (8 bytes per entry: fp32, or fp64 for PM_SPLIT3): the
+// split-K partials (8 bytes per entry: fp32, or fp64 for PM_F64): the
 // largest of all weight-gradient launches of a plan.  Gx groups per launch.
 static void plan_partials(Carver& cv, StepPlan& pl, const pigan_step_desc* s, bool trunk, int Gg, int GD) {
   int64_t mx = 0, mxb = 0;
@@ -502,7 +502,7 @@ static pigan_status gemm_nt(int epi, int nd1, int nd2, const NtArgs<T>& a, int G
   return PIGAN_OK;
 }
 
-// part: the plan's split-K partial buffer (fp32 entries, or fp64 for PM_SPLIT3)
+// part: the plan's split-K partial buffer (fp32 entries, or fp64 for PM_F64)
 template <class T>
 static pigan_status weight_grad(const T* dA, int64_t a_g, int64_t lda, const T* H, int64_t h_g, int64_t ldh,
                                 int64_t R, int64_t n_value, int N, int Jp, int J, float* gW, float* gb, int64_t g_g,
