@@ -781,18 +781,19 @@ k_gemm_nt(const NtArgs<T> p) {
     for (int k = 0; k < C; ++k) load_frag(raw[k], src, u, k, t, k > 0 && seeds);
     __builtin_amdgcn_sched_barrier(0);   // all in flight together
   };
+  auto add_row = [&](FragRaw<T>& raw, int u, int k, int t) {
+    frag_unswap<T>(raw);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      float v[4];
+      frag_group<T>(raw, q, v);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[u][k][t][4 * q + e] += v[e];
+    }
+  };
   auto add_rows = [&](FragRaw<T>* raw, int u, int t) {
 #pragma unroll
-    for (int k = 0; k < C; ++k) {
-      frag_unswap<T>(raw[k]);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float v[4];
-        frag_group<T>(raw[k], q, v);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[u][k][t][4 * q + e] += v[e];
-      }
-    }
+    for (int k = 0; k < C; ++k) add_row(raw[k], u, k, t);
   };
 
   if (EPI == EPI_FWD) {
@@ -867,9 +868,15 @@ k_gemm_nt(const NtArgs<T> p) {
             if constexpr (AHEAD) {
               add_rows(sk, u, t);
             } else {
-              FragRaw<T> late[C];
-              load_rows(late, p.skip, u, t);
-              add_rows(late, u, t);
+              // (a stream at a time: all five beside the accumulators spilled ten registers of the
+              // 64 x 256 tile, also where there is no skip)
+#pragma unroll
+              for (int k = 0; k < C; ++k) {
+                FragRaw<T> late;
+                load_frag(late, p.skip, u, k, t);
+                add_row(late, u, k, t);
+                __builtin_amdgcn_sched_barrier(0);
+              }
             }
           }
           store_rows(p.out_h, u, t);
@@ -959,6 +966,14 @@ k_gemm_nt(const NtArgs<T> p) {
             av[k] = ap[k][e];
           }
           jet_bwd<ND1, ND2, X64>(gv, av);
+          // (fp64: an element's results are formed before the next one's; left
+          // to itself the compiler evaluates one exponential of all sixteen
+          // first and spills what is left of them, 8 and 25 registers with two
+          // and four streams)
+          if constexpr (X64) {
+#pragma unroll
+            for (int k = 0; k < C; ++k) asm volatile("" : "+v"(gv[k]));
+          }
 #pragma unroll
           for (int k = 0; k < C; ++k) acc[u][k][t][4 * q + e] = gv[k];
           if (X64 && e % 2 == 1) __builtin_amdgcn_sched_barrier(0);
@@ -2534,13 +2549,15 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
           // 42.0 against 45.1, reverse 40.2 against 40.4; 262,144 rows: 122
           // against 110, reverse 108 against 99)
           if constexpr (C == 1) {
-            if (a.N == 128 && npts * G >= 196608 && a.K % 32 == 0) {
-              dim3 grid((unsigned)((npts + 127) / 128), 1, G);
-              k_gemm_nt<T, ND1, ND2, 2, 2, 2, 2, EPI, 2, true, false, PM_SPLIT2, 2, 2><<<grid, 256, 0, st>>>(a);
-            } else {
-              dim3 grid((unsigned)(((npts + 63) / 64) * ((a.N + 127) / 128)), 1, G);
-              k_gemm_nt<T, ND1, ND2, 2, 2, 1, 2, EPI, 2, true, false, PM_SPLIT2><<<grid, 256, 0, st>>>(a);
+            if constexpr (EPI != EPI_DF) {
+              if (a.N == 128 && npts * G >= 196608 && a.K % 32 == 0) {
+                dim3 grid((unsigned)((npts + 127) / 128), 1, G);
+                k_gemm_nt<T, ND1, ND2, 2, 2, 2, 2, EPI, 2, true, false, PM_SPLIT2, 2, 2><<<grid, 256, 0, st>>>(a);
+                return hipGetLastError();
+              }
             }
+            dim3 grid((unsigned)(((npts + 63) / 64) * ((a.N + 127) / 128)), 1, G);
+            k_gemm_nt<T, ND1, ND2, 2, 2, 1, 2, EPI, 2, true, false, PM_SPLIT2><<<grid, 256, 0, st>>>(a);
           }
         } else if (a.pm == PM_SPLIT2) {
           // 64 points x 64 NTM columns, 2 x 2 waves
