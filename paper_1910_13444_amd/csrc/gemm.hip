@@ -246,10 +246,8 @@ typedef __attribute__((address_space(3))) void* lds_ptr_t;
 // two 64-byte slices back to back: a cache line then crosses from L2 once
 // (measured with every block reading L2-resident rows: 18.3 TB/s over the chip
 // for single 64-byte slices, 34.8 TB/s in pairs).
-// OUT (with RING): the output layer fused in place of the activations' store,
-// which took one write and one read of every top activation (whole steps of
-// 16 x 256-wide, 512-wide and 1024-wide generators 63.9 -> 62.4, 36.2 -> 35.8
-// and 164.1 -> 163.5 ms).
+// OUT (with RING): the output layer fused in place of the activations' store
+// (nt_ring_out_ok: where this pays, with figures).
 // PM (fp32 storage only): products from bf16 pieces of the fp32 operands
 // (ProdMode).
 // p.kx > 0 (two-term weights): operand X is kx wide, the weight rows
@@ -2461,11 +2459,21 @@ bool nt_resident_ok(int elem_bytes, int C, int K, int N, int64_t n_points, int64
   return elem_bytes == 2 && C >= 1 && C <= 5 && K == 128 && N == 128 && span < ((int64_t)1 << 31);
 }
 
-// (three streams and more: one and two stay on the large tiles, which are
-// slower with the output layer fused: field evaluation of 512-wide generators,
-// value rows only, 8.34 ms fused, 7.17 apart)
+// The fused launch saves one write and one read of every top activation, but
+// runs on the 32 x 128 tile: on the large ones the column weights push the
+// accumulators out of the register file (five streams at K = 512 1917 us, three
+// 1854).  us per launch, fused | the faster tile and a separate pass, 262,144
+// points at K = N = 256 and 512, 131,072 at 768 and 1024, 32,768 at 2048:
+//            K = 256     512           768           1024          2048
+//   C = 3    407 | 502   1225 | 1200   1208 | 1135   2055 | 1813   1935 | 1596
+//   C = 4    461 | 646   1338 | 1771   1440 | 1775   2280 | 2818   2201 | 2589
+//   C = 5    575 | 805   1725 | 2040   1736 | 1989   2882 | 3059   2807 | 2724
+//   C = 7    964 | 1110  2963 | 2980   3205 | 3076   5124 | 4694   4743 | 4162
+// One and two streams stay on the large tiles (value fields of width 512, 8.34
+// ms fused, 7.17 apart).
 bool nt_ring_out_ok(int elem_bytes, int C, int K, int N, int64_t n_points) {
-  return elem_bytes == 2 && C >= 3 && C <= 7 && K == N && N >= 128 && N % 128 == 0 && n_points > 0 &&
+  const bool pays = C == 4 || (C == 5 && N <= 1024) || ((C == 3 || C == 7) && N <= 256);
+  return elem_bytes == 2 && pays && K == N && N >= 128 && N % 128 == 0 && n_points > 0 &&
          !nt_resident_ok(elem_bytes, C, K, N, n_points, K, N);
 }
 
@@ -2616,30 +2624,32 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
   } else if (ring_ok<T, C, EPI>(a)) {
     // 16-bit layers of 128 columns and more (128 itself: what the resident
     // kernel does not take): operand stages straight into LDS.  Large tiles
-    // read every operand fewer times and suit the matrix-core-bound depths;
-    // 32 points x 128 columns (four waves, two blocks per CU for up to five
-    // streams, so that one block's epilogue runs beside the other's products)
-    // suits launches that would give the chip fewer than two rounds of large
-    // tiles, five streams at K = 256 (HBM-bound) and every reverse pass of
-    // five streams.  us per launch, K = N = 256 / 512 (262,144 points) / 1024
-    // (131,072), before -> now (large tile | 32 x 128):
-    //   forward  C = 5:  737 / 1812 / 2977 ->  651 / 1637 / 2619 |  599 / 1755 / 2930
-    //            C = 3:  436 / 1205 / 1986 ->  404 / 1020 / 1690 |  425 / 1210 / 2118
-    //            C = 1:  719 / 2080 / 3251 ->  545 / 1492 / 2317 (4 x the points)
-    //   reverse  C = 5:  554 / 1425 / 2152 ->  568 / 1446 / 2022 |  480 / 1217 / 1869
-    //            C = 3:    - /  862 / 1242 ->  330 /  772 / 1109 |  318 /  881 / 1312
+    // (eight waves) read every operand fewer times and suit the
+    // matrix-core-bound depths; 32 points x 128 columns (four waves, two blocks
+    // per CU for up to five streams, so that one block's epilogue runs beside
+    // the other's products) suits launches that would give the chip fewer than
+    // two rounds of large tiles, and where the figures say so.  us per launch,
+    // large | 32 x 128, points as in nt_ring_out_ok's table:
+    //                K = N = 256   512           768           1024          2048
+    //   forward C=1    528 | 725   1378 | 2126   1311 | 2191   2198 | 4175   1960 | 8610   (4 x the points)
+    //           C=2    300 | 334   725 | 909     687 | 947     1112 | 1595   968 | 1597
+    //           C=3    405 | 452   1010 | 1370   982 | 1341    1630 | 2149   1472 | 2039
+    //           C=4    575 | 521   1700 | 1548   1715 | 1606   2836 | 2601   2570 | 2439
+    //           C=5    700 | 670   1730 | 1922   1732 | 1951   2757 | 3119   2513 | 2954
+    //           C=7    900 | 1062  2590 | 3114   2780 | 3348   4312 | 5404   3905 | 4889
+    //   reverse C=2    235 | 214   580 | 556     535 | 546     831 | 879     685 | 837
+    //           C=3    308 | 310   751 | 877     700 | 842     1087 | 1317   907 | 1153
+    //           C=4    432 | 374   1193 | 1030   1100 | 940    1800 | 1514   1540 | 1321
+    //           C=5    568 | 480   1446 | 1217                 2022 | 1869
+    // (seven streams reverse: 32 x 128 only)
     if constexpr (sizeof(T) == 2) {
       constexpr bool FWD = EPI == EPI_FWD;
       constexpr int WM = C == 1 ? 4 : 2, WN = C == 1 ? 2 : 4, MT = C <= 3 && FWD ? 2 : 1, NT = C == 1 ? 4 : (C <= 3 || C == 5 ? 2 : 1);
       constexpr int BM = 32 * MT * WM, BN = 32 * NT * WN;
       const int64_t blocks = ((npts + BM - 1) / BM) * ((a.N + BN - 1) / BN) * G;
-      // (with the output layer fused the large tiles take up to twice as long,
-      // five streams at K = 512 1917 us against 1520 on the small one, three
-      // 1854 against 1094: the column weights push the accumulators out of the
-      // register file)
-      const bool large = !a.y && a.N >= 256 && blocks >= 2 * (int64_t)cu_count() && !(C == 5 && (!FWD || a.N == 256)) &&
-                         !(C == 3 && !FWD && a.N == 256);
-      if constexpr (FWD || C <= 4) {
+      constexpr int LARGE_N = FWD ? (C == 5 ? 512 : 256) : (C == 2 ? 768 : 512);   // narrowest that takes the large tile
+      const bool large = !a.y && a.N >= LARGE_N && blocks >= 2 * (int64_t)cu_count();
+      if constexpr (C != 4 && (FWD || C <= 3)) {
         if (large) {
           dim3 grid((unsigned)(((npts + BM - 1) / BM) * ((a.N + BN - 1) / BN)), 1, G);
           k_gemm_nt<T, ND1, ND2, WM, WN, MT, NT, EPI, 1, true, true, PM_NATIVE, 2><<<grid, 64 * WM * WN, 0, st>>>(a);
