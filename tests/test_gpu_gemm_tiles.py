@@ -3,7 +3,9 @@ from its streams, depth and number of points, and every tile multiplies in the
 same order, so a point's jets do not depend on how many points share its call.
 Each case evaluates a few points alone (32-point tiles), compares them with
 the oracle, and again at the front and the back of a call large enough for the
-large tiles, whose last tile is ragged: bit for bit the same."""
+large tiles, whose last tile is ragged: bit for bit the same.  (Four streams,
+five at 256 columns and seven at 128 take the 32-point tile at every size:
+there the large call is that tile in more blocks.)"""
 import numpy as np
 import pytest
 
@@ -149,3 +151,33 @@ def test_output_layer_sum_order(d, order, W, pts, dtype):
     got = got.cpu().numpy()[0].reshape(-1, pts)
     assert (got[0] == lane[0] + b_out).all(), (got[0][0], lane[0] + b_out)
     assert (got[1:] == 0).all()
+
+
+# Split products (16-bit modes) of the critic: every kernel that forms them adds
+# in the same order, so a snapshot's score does not depend on how many share its
+# call.  Forty snapshots alone (short launches) against the oracle, and again at
+# the front and the ragged back of a batch that each tiled kernel takes (32,
+# 64, 128 and 1024 columns; 128 above 196,608 rows; 256 columns and more from
+# 16,384 rows, contractions of both sides of 512).  The bound pins the low
+# pieces: two bf16 pieces carry 16 bits (2^-17 per operand, 2^-16 per product),
+# and the sums of a score cancel by about a factor of six; without a low piece
+# the error is 2^-9.
+@pytest.mark.parametrize("n_in,L,W,B", [(40, 2, 32, 17001), (40, 2, 64, 17001), (100, 2, 128, 17001),
+                                        (96, 2, 128, 196673), (100, 2, 256, 16421), (64, 2, 512, 16421),
+                                        (2016, 2, 1024, 2009)])
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+def test_disc_forward_split_tiles(dtype, n_in, L, W, B):
+    import torch
+    print(f"disc_forward split tiles n_in={n_in} W={W} B={B} {dtype}", flush=True)
+    rng = np.random.default_rng(n_in + W)
+    few, shape = 40, (n_in, L, W)
+    p = glorot_mlp(rng, *shape)[None]
+    snap = rng.standard_normal((1, B, n_in)).astype(np.float32)
+    snap[0, -few:] = snap[0, :few]
+    small = pigan.disc_forward(to_dev(p), shape, to_dev(snap[:, :few]), dtype=dtype)
+    large = pigan.disc_forward(to_dev(p), shape, to_dev(snap), dtype=dtype)
+    torch.cuda.synchronize()
+    ref = oracle.mlp_forward(p[0], shape, snap[0, :few])
+    check({"score": rel(small.cpu().numpy()[0], ref)}, 1e-4, f"split products {dtype}")
+    assert torch.equal(small[0], large[0, :few])
+    assert torch.equal(small[0], large[0, -few:])
