@@ -2516,7 +2516,8 @@ hipError_t nt_dispatch_tile(const NtArgs<T>& a, int G, hipStream_t st) {
     // split products (the critic and the generators' sensor rows): one or two
     // streams; register-staged tiles
     if (a.pm != PM_NATIVE) {
-      if (a.y || a.fp1) return hipErrorInvalidValue;
+      // (nor one row per stream: the short kernels read whole ones)
+      if (a.y || a.fp1 || a.a_seeds) return hipErrorInvalidValue;
       if constexpr (C <= 2) {
         // few output tiles.  us per forward launch, tiled -> short, rows x N x K
         // (number of 32 x 32 blocks): split products 512 x 256 x 416 (128)

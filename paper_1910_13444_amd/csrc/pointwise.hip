@@ -1402,7 +1402,11 @@ hipError_t launch_cast_layers(const CastSet<T>& c0, const CastSet<T>& c1, int G,
   auto blocks = [](const CastSet<T>& c) { return (int64_t)c.layers * ((c.Kp + 31) / 32) * ((c.N + 31) / 32); };
   const int64_t b0 = blocks(c0), b1 = blocks(c1);
   if (b0 + b1 <= 0) return hipSuccess;
-  if (b0 + b1 > 0x7fffffff) return hipErrorInvalidValue;
+  // split copies: whole 16-element blocks in every row written
+  auto whole = [](const CastSet<T>& c) {
+    return c.layers <= 0 || !c.pair || (c.Kp % 16 == 0 && (!c.fT || c.N % 16 == 0));
+  };
+  if (b0 + b1 > 0x7fffffff || !whole(c0) || !whole(c1)) return hipErrorInvalidValue;
   k_cast_layers<T><<<dim3((unsigned)(b0 + b1), 1, G), 256, 0, st>>>(c0, c1, (int)b0);
   return hipGetLastError();
 }
