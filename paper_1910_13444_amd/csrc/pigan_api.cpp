@@ -491,12 +491,22 @@ static pigan_status gemm_nt(int epi, int nd1, int nd2, const NtArgs<T>& a, int G
   // operand X is read unless the first layer is formed in the kernel (then
   // its activations may be stored instead)
   double bytes = ((a.fp1 ? (a.f_out_h ? M * Ka : 0.0) : M * Ka) + (double)a.N * a.K) * es * G;
-  if (epi == EPI_FWD) bytes += M * a.N * es * G * ((a.out_a ? 1 : 0) + (a.out_h ? 1 : 0)) + (a.y ? M * 4.0 * G : 0.0);
-  else if (epi == EPI_BWD) bytes += (a.fp1 ? 1.0 : 2.0) * M * a.N * es * G;
+  // (ypart: the fused output layer's sums of 128 columns, written and read back
+  // where there is more than one)
+  const bool ring_out = epi == EPI_FWD && a.y && a.ypart;
+  if (epi == EPI_FWD)
+    bytes += M * a.N * es * G * ((a.out_a ? 1 : 0) + (a.out_h ? 1 : 0) + (a.skip ? 1 : 0)) + (a.y ? M * 4.0 * G : 0.0) +
+             (ring_out && a.N > 128 ? 2.0 * M * (a.N / 128) * 4.0 * G : 0.0);
+  else if (epi == EPI_BWD)   // cotangents out; pre-activations in (a_seeds: value rows and one row per stream)
+    bytes += (M * ((a.skip_g ? 2 : 1) + (a.out_gh ? 1 : 0)) +
+              (a.fp1 ? 0.0 : a.a_seeds ? (double)a.seg.n_points + (C - 1) : M)) * a.N * es * G;
   else bytes += M * a.N * 4.0 * G;
-  // timing records are keyed by launch shape: one name = one kernel instantiation and size
+  // timing records are keyed by launch shape: one name, one size.  Launches of the ring kernels with the output
+  // layer fused (another tile, and k_out_sum) have a name of their own; the resident kernel's first- and last-layer
+  // forms (128 columns, 16-bit storage) share their layer's
   char key[64];
-  snprintf(key, sizeof key, "%s_c%d_k%d_n%d%s%s", name, C, Ka, a.N, pm_tag(a.pm), a.kx > 0 ? "_w2" : "");
+  snprintf(key, sizeof key, "%s_c%d_k%d_n%d%s%s%s", name, C, Ka, a.N, pm_tag(a.pm), a.kx > 0 ? "_w2" : "",
+           ring_out ? "_out" : "");
   ProfScope ps(st, key, flops, bytes);
   HIP_TRY(launch_gemm_nt<T>(epi, nd1, nd2, a, G, st));
   return PIGAN_OK;

@@ -52,3 +52,30 @@ def test_step_large_tiles(kind, d, W, S, P, n_s):
     assert out["nonfinite"] == 0 and parts["nonfinite"] == 0
     check(errors(wl, out, parts), 1e-5, "whole against chunks")
     check(errors(wl, out, ref(wl, inp, real)), 3e-3, "whole against the oracle")
+
+
+# The timing records' byte model of five streams at 256 columns: a reverse pass
+# into the first layer reads its value rows and one row per further stream; the
+# fused last layer has a name of its own, writes no activations, and its sums of
+# 128 columns cross twice.
+def test_profile_bytes_of_seeds_and_fused_output():
+    from paper_1910_13444_amd import pigan
+    print("profile bytes d=2 W=256", flush=True)
+    wl = BASE.with_(d=2, W=256, dtype="bf16")
+    inp = make_inputs(wl, f_array=True)
+    real = oracle.real_snapshots(wl, inp)
+    pigan.profile_enable(True)
+    try:
+        run_step_gpu(wl, inp, real)
+        stats = {s["name"]: s for s in pigan.profile_read()}
+    finally:
+        pigan.profile_enable(False)
+    n, W, C = wl.S * wl.P, wl.W, 5
+    M, weights = C * n, W * W * 2
+    bwd = [M * W * 2 + weights + M * W * 2 + rows * W * 2 for rows in (M, n + C - 1)]   # X, weights, out, saved rows
+    assert stats["gemm_bwd_c5_k256_n256"]["launches"] == 2
+    assert stats["gemm_bwd_c5_k256_n256"]["bytes"] == sum(bwd)
+    assert stats["gemm_fwd_c5_k256_n256_w2"]["bytes"] == M * W * 2 + 2 * weights + 2 * M * W * 2
+    out = stats["gemm_fwd_c5_k256_n256_w2_out"]
+    assert out["launches"] == 1
+    assert out["bytes"] == M * W * 2 + 2 * weights + M * W * 2 + M * 4 + 2 * M * (W // 128) * 4
