@@ -172,7 +172,7 @@ enum EpiMode { EPI_FWD = 0, EPI_BWD = 1, EPI_DF = 2 };
 template <class T> struct NtArgs {
   const T* X;  int64_t x_g;  int64_t ldx;  // A operand rows (activations)
   const T* Wm; int64_t w_g;  int64_t ldw;  // B operand rows: [N x K] row-major
-  const float* bias; int64_t b_g;         // EPI_FWD: bias on stream 0
+  const float* bias; int64_t b_g;         // EPI_FWD: bias on stream 0 (required)
   T* out_a;  T* out_h; int64_t o_g; int64_t ldo;  // EPI_FWD: pre-activation / activation
   const T* aprev;                          // EPI_BWD: saved pre-activation of the layer below
   // EPI_BWD: aprev is the first layer's, whose derivative streams are the same
@@ -199,13 +199,14 @@ template <class T> struct NtArgs {
   const float* fzp; int64_t fzp_g;
   const float* fx; int64_t fx_g; int32_t fx_shared; int64_t fPn;
   T* f_out_h;                              // forward: also store the generated activations (may be null)
-  // residual blocks of a shared trunk (tiled kernels only).  EPI_FWD: skip
+  // residual blocks of a shared trunk (tiled and resident kernels).  EPI_FWD: skip
   // (the activations of layer l - 2, every stream) is added to the
   // activations.  EPI_BWD: skip_g (the total activation cotangent carried
   // back by a skip) is added to the product, and out_gh, when set, receives
-  // that total before the reverse carry; out_gh may alias skip_g (a block
-  // reads its whole tile of skip_g before the barrier that precedes its
-  // stores, and tiles are disjoint).
+  // that total before the reverse carry; out_gh may alias skip_g (the tiled
+  // kernels: a lane stores the row pieces that it has read itself; the resident
+  // kernel reads its whole tile of skip_g before the barrier that precedes its
+  // stores; tiles are disjoint).
   const T* skip; const T* skip_g; T* out_gh;
   // EPI_DF: seeds per point are sY_ld / sU_ld apart (0: nY / nU) and the u
   // seeds start sU_off entries into a point's row
@@ -243,8 +244,9 @@ hipError_t launch_gemm_dw(const T* dA, int64_t a_g, int64_t lda, const T* H, int
 // offsets)
 bool nt_resident_ok(int elem_bytes, int C, int K, int N, int64_t n_points, int64_t ldx, int64_t ldo);
 
-// whether launch_gemm_nt runs this shape's forward on the ring kernels, which
-// can fuse the output layer too (16-bit storage, two-term weights)
+// whether launch_gemm_nt should form the output layer in the last hidden
+// layer's ring kernel (16-bit storage, two-term weights, three streams and
+// more): where that is faster than a pass of its own
 bool nt_ring_out_ok(int elem_bytes, int C, int K, int N, int64_t n_points);
 
 void dw_split_plan(int64_t R, int N, int J, int elem_bytes, int G, int* n_split, int64_t* rows_per_split);

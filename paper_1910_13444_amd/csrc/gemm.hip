@@ -42,7 +42,7 @@ namespace pigan {
 // the writes).
 static constexpr int LDS_PITCH = 64;
 // registers of accumulators, fragments and saved pre-activations up to which the
-// ring kernels read their fragments one chunk ahead
+// ring kernels issue their fragment reads one chunk ahead (PIPE)
 static constexpr int PIPE_REGS = 200;
 typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -597,8 +597,14 @@ k_gemm_nt(const NtArgs<T> p) {
 #pragma unroll
           for (int t = 0; t < NT; ++t) Elem<T>::mma(acc[u][k][t], wf[b][t], xf[b][u][k]);   // rows: columns n; cols: points
     };
-    // PIPE (where the registers allow it): the fragments of a 16-wide chunk
-    // are read one chunk ahead of their products, across the stage barrier too
+    // PIPE (where the registers allow it): the reads of a 16-wide chunk's
+    // fragments are issued before the products of the chunk before, across the
+    // stage barrier too.  They do not stay ahead: while a direct-to-LDS load is
+    // outstanding the compiler drains every LDS read before a use (all 212
+    // waits of these kernels' product loops are lgkmcnt(0)), so two of a stage's
+    // four chunks wait for their successor's fragments as well, and what is
+    // gained is one wait for two chunks.  Without it: seven streams at 128
+    // columns 1.40 -> 1.46 ms (3-D residual), widths 256 to 1024 within 1 %.
     constexpr bool PIPE = MT * C * NT * 16 + 8 * (MT * C + NT) + (PRE ? 8 * MT * C * NT : 0) <= PIPE_REGS;
     if constexpr (PIPE) {
       issue(0);
@@ -733,7 +739,7 @@ k_gemm_nt(const NtArgs<T> p) {
   // (regs 4q..4q+3), four consecutive columns 8q + 4*(lane >> 5) + 0..3 of
   // every 32x32 tile: all jet streams of a (point, column) sit in the same
   // lane.  Results leave straight from the registers as 16-byte row pieces
-  // (frag_store): staging every stream through LDS took two barriers per
+  // (store_rows): staging every stream through LDS took two barriers per
   // stream and array, which on the one-block-per-CU tiles nothing overlapped.
   if (EPI == EPI_DF) {
     const int64_t ldY = p.sY_ld > 0 ? p.sY_ld : p.nY, ldU = p.sU_ld > 0 ? p.sU_ld : p.nU;
@@ -2444,15 +2450,13 @@ k_gemm_dw_tr(const T* __restrict__ dA, int64_t a_g, int64_t lda, const T* __rest
 // ---------------------------------------------------------------------------
 // host launchers
 // ---------------------------------------------------------------------------
-namespace {
-
-// Tiles.  A wave owns 32 points x 32*NT columns of every stream.  Layers
-// below the wide path: NT = 4 / 2 / 1 for 1 / 2 / 3+ streams (2 x 2 waves,
-// two waves per SIMD), and 4 x 1 waves for narrow layers (N <= 32).  The wide
-// path (K, N >= 256) stages operands straight into an LDS ring, which
-// hides the load latency that otherwise bounds it, and uses the block shapes
-// measured fastest per stream count.
-}  // namespace
+// Tiles.  A wave owns 32 points x 32*NT columns of every stream.  16-bit
+// forwards (two-term weights) and reverse passes of 128 columns and more whose
+// contraction is whole 128-byte slices take the ring kernels (ring_ok), 128 x
+// 128 layers of up to five streams the resident kernel; fp32-stored products of
+// one and two streams with few output tiles the short kernels.  The others are
+// register-staged: NT = 4 / 2 / 1 for 1 / 2 / 3+ streams (2 x 2 waves, two waves
+// per SIMD), and 4 x 1 waves for narrow layers (N <= 32).
 
 bool nt_resident_ok(int elem_bytes, int C, int K, int N, int64_t n_points, int64_t ldx, int64_t ldo) {
   const int64_t span = (n_points + 1) * (ldx > ldo ? ldx : ldo) * (int64_t)elem_bytes;
