@@ -2473,10 +2473,11 @@ bool nt_resident_ok(int elem_bytes, int C, int K, int N, int64_t n_points, int64
 //   C = 4    461 | 646   1338 | 1771   1440 | 1775   2280 | 2818   2201 | 2589
 //   C = 5    575 | 805   1725 | 2040   1736 | 1989   2882 | 3059   2807 | 2724
 //   C = 7    964 | 1110  2963 | 2980   3205 | 3076   5124 | 4694   4743 | 4162
-// One and two streams stay on the large tiles (value fields of width 512, 8.34
-// ms fused, 7.17 apart).
+// (Five streams at 1024 and 262,144 points: 6.02 | 5.96 ms, the 6 x 1024 step
+// 1783 | 1778 ms.)  One and two streams stay on the large tiles (value fields of
+// width 512, 8.34 ms fused, 7.17 apart).
 bool nt_ring_out_ok(int elem_bytes, int C, int K, int N, int64_t n_points) {
-  const bool pays = C == 4 || (C == 5 && N <= 1024) || ((C == 3 || C == 7) && N <= 256);
+  const bool pays = C == 4 || (C == 5 && N <= 768) || ((C == 3 || C == 7) && N <= 256);
   return elem_bytes == 2 && pays && K == N && N >= 128 && N % 128 == 0 && n_points > 0 &&
          !nt_resident_ok(elem_bytes, C, K, N, n_points, K, N);
 }
