@@ -120,10 +120,15 @@ __device__ __forceinline__ int frag_col(int lane, int i) {
   return sizeof(T) == 2 ? 16 * ((lane >> 4) & 1) + 8 * (lane >> 5) : 16 * i + 8 * ((lane >> 4) & 1) + 4 * (lane >> 5);
 }
 
+// both values rounded to the storage type, together: converted one at a time,
+// fp16 results come from v_fma_mixlo_f16, which rounds the last operation to
+// 16 bits at once and not after its fp32 rounding (80 of them in the five-stream
+// reverse epilogue: other values in rare cases, and two instructions a pair)
 template <class T>
 __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
-  return (uint32_t)__builtin_bit_cast(uint16_t, Elem<T>::from_f(lo)) |
-         ((uint32_t)__builtin_bit_cast(uint16_t, Elem<T>::from_f(hi)) << 16);
+  typedef T T2 __attribute__((ext_vector_type(2)));
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), T2));
 }
 
 // products layout -> pieces
