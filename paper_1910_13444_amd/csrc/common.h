@@ -186,8 +186,9 @@ template <class T> struct NtArgs {
   // nt_resident_ok or nt_ring_out_ok holds): y[row] = w_out . h (+ b_out on the value stream),
   // rows in the activation row layout; wout = [w_out (N), b_out]
   float* y; int64_t y_g; const float* wout; int64_t wo_g;
-  // the ring kernels' fused output layer: out_h is not written; sums of 128
-  // columns go to ypart (yp_g floats per group, at least N / 128 per row)
+  // the ring kernels' fused output layer (ypart != null): out_h is not written;
+  // with more than 128 columns, sums of 128 of them go to ypart (yp_g floats per
+  // group, at least N / 128 per row)
   float* ypart; int64_t yp_g;
   // second-layer calls with the first layer formed in the kernel (only where
   // nt_resident_ok holds; fp1 != null): the forward builds its operand X,
